@@ -739,8 +739,6 @@ TIMELINE_PHASES = {   # phase marks (record words 2..5) of the instrumented kern
     "k_window": ("wave 0 scanned", "block totals combined", "windows chosen"),
     "k_hist_merge": ("rows summed",),
     "k_grad_top": ("rows summed (G loaded)", "patterns done", "block summed"),
-    "k_fwd_iter": ("loads issued", "partials summed, C formed", "patterns done", "block summed"),
-    "k_bwd_iter": ("loads issued", "partials summed, gamma formed", "patterns done", "block summed"),
 }
 
 

@@ -23,6 +23,7 @@ constexpr int ROW4 = 2 * W4;          // 32-bit words per N-pass partial row
 constexpr int T_WG = 64;              // table-phase workgroups per matrix (a multiple of 64)
 constexpr int T_THREADS = 256;
 constexpr int T_KPT = NKEYS / (T_WG * T_THREADS);   // patterns per table-phase thread
+constexpr int TOP_ROWS = 760;         // rows of the backward's first sums, at most
 constexpr int KMAX = 16;
 constexpr int PSTRIDE = 32;           // floats per table-phase partial row (2 * KMAX)
 constexpr int MAXB = EDKM_LAUNCH_GROUP;   // matrices per launch
@@ -46,19 +47,20 @@ struct DevState {
 struct Ws {
     uint32_t* counts;   // [NKEYS]
     float* tab;         // [NKEYS]  W~ value per pattern
-    float* H;           // [NKEYS]  dW~/dw per pattern (through the final softmax)
-    float* R;           // [NKEYS]  accumulated R during the backward
-    float2* HR;         // [NKEYS]  (H, R) for the gradient gather
+    float2* HR;         // [NKEYS]  per pattern: H = dW~/dw through the final softmax (the
+                        // forward's), R through the centroids (the backward's)
     float* G;           // [NKEYS]  keyed gradient sums outside the LDS window
     float* chist;       // [(max_iter+1) * KMAX]  C^(t)
     float* shist;       // [(max_iter+1) * KMAX]  S^(t)
     float* ghist;       // [(max_iter+1) * KMAX]  dL/dC^(t)
-    float* ehist;       // [KMAX]  direct-use term of the dense backward
-    float* cfin;        // [2 * KMAX]  C^(T-1), C^(T) of the last forward (at a fixed place)
-    float* tpart;       // [(max_iter+1) * T_WG * PSTRIDE]  forward table partials
-    float* bpart;       // [(max_iter+1) * T_WG * PSTRIDE]  backward table partials
+    float* ehist;       // [KMAX]  direct-use term E of the backward (the dense one's with the 1/tau)
+    uint32_t* fx;       // [max_iter * T_WG * 2 * KMAX]  forward table phase: rows exchanged between blocks
+    uint32_t* bx;       // [(max_iter + 2) * T_WG * KMAX]  the same of the backward: its iterations', its first sums'
+    float* tx;          // [TOP_ROWS * 2 * KMAX]  backward: first sums (k_grad_top's rows)
+    float* bpart;       // [T_WG * PSTRIDE]  backward: the partials of t = 1
     float* dpart;       // [D_WG * PSTRIDE]  dense-path partials
     int2* span;         // [NP_MAX_WG]  histogram partial spans
+    float* cfin;        // [2 * KMAX]  C^(T-1), C^(T) of the last forward (at a fixed place)
     uint32_t* part;     // [NP_MAX_WG * ROW4]  N-pass partial rows
     uint8_t* pidx;      // [NKEYS]  palettization: nearest lookup-table entry per pattern
     uint16_t* rank;     // [NKEYS]  occupied patterns below each pattern (unique_inverse)
@@ -127,7 +129,7 @@ static_assert(sizeof(BatchArgs) <= 4096, "launch arguments fit the kernel-argume
 // function of max_iter only, evaluated on the host (sizing, plan checks) and
 // in every kernel (from the workspace base in the launch arguments).
 struct Layout {
-    size_t counts, tab, H, R, HR, G, chist, shist, ghist, ehist, cfin, tpart, bpart, dpart, span, part, pidx,
+    size_t counts, tab, HR, G, chist, shist, ghist, ehist, cfin, fx, bx, tx, bpart, dpart, span, part, pidx,
         rank, st, total;
 };
 
@@ -136,12 +138,10 @@ __host__ __device__ inline Layout layout(int max_iter) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = (o + bytes + 255) & ~size_t(255); return at; };
     const size_t hist = (size_t)(max_iter + 1) * KMAX * sizeof(float);
-    const size_t tp = (size_t)(max_iter + 1) * T_WG * PSTRIDE * sizeof(float);
+    const size_t row = (size_t)max_iter * T_WG * KMAX * sizeof(uint32_t);
     L.st = take(sizeof(DevState));
     L.counts = take(NKEYS * sizeof(uint32_t));
     L.tab = take(NKEYS * sizeof(float));
-    L.H = take(NKEYS * sizeof(float));
-    L.R = take(NKEYS * sizeof(float));
     L.HR = take(NKEYS * sizeof(float2));
     L.G = take(NKEYS * sizeof(float));
     L.chist = take(hist);
@@ -149,8 +149,10 @@ __host__ __device__ inline Layout layout(int max_iter) {
     L.ghist = take(hist);
     L.ehist = take(KMAX * sizeof(float));
     L.cfin = take(2 * KMAX * sizeof(float));
-    L.tpart = take(tp);
-    L.bpart = take(tp);
+    L.fx = take(2 * row);
+    L.bx = take(row + (size_t)2 * T_WG * KMAX * sizeof(uint32_t));
+    L.tx = take((size_t)TOP_ROWS * 2 * KMAX * sizeof(float));
+    L.bpart = take((size_t)T_WG * PSTRIDE * sizeof(float));
     L.dpart = take((size_t)D_WG * PSTRIDE * sizeof(float));
     L.span = take(NP_MAX_WG * sizeof(int2));
     L.part = take((size_t)NP_MAX_WG * ROW4 * sizeof(uint32_t));
@@ -171,16 +173,16 @@ __host__ __device__ inline Ws carve_workspace(void* base, int max_iter) {
     w.st = reinterpret_cast<DevState*>(c + L.st);
     w.counts = reinterpret_cast<uint32_t*>(c + L.counts);
     w.tab = reinterpret_cast<float*>(c + L.tab);
-    w.H = reinterpret_cast<float*>(c + L.H);
-    w.R = reinterpret_cast<float*>(c + L.R);
     w.HR = reinterpret_cast<float2*>(c + L.HR);
     w.G = reinterpret_cast<float*>(c + L.G);
     w.chist = reinterpret_cast<float*>(c + L.chist);
     w.shist = reinterpret_cast<float*>(c + L.shist);
     w.ghist = reinterpret_cast<float*>(c + L.ghist);
     w.ehist = reinterpret_cast<float*>(c + L.ehist);
+    w.fx = reinterpret_cast<uint32_t*>(c + L.fx);
+    w.bx = reinterpret_cast<uint32_t*>(c + L.bx);
     w.cfin = reinterpret_cast<float*>(c + L.cfin);
-    w.tpart = reinterpret_cast<float*>(c + L.tpart);
+    w.tx = reinterpret_cast<float*>(c + L.tx);
     w.bpart = reinterpret_cast<float*>(c + L.bpart);
     w.dpart = reinterpret_cast<float*>(c + L.dpart);
     w.span = reinterpret_cast<int2*>(c + L.span);
@@ -208,8 +210,8 @@ hipError_t noalloc_scratch(uint8_t** out);
 // On failure *where names the launch that failed.
 hipError_t launch_init_unique(BatchArgs& b, uint32_t grid_np, hipStream_t s, const char** where,
                               const PassEvents* ev = nullptr);
-hipError_t launch_forward(BatchArgs& b, uint32_t grid_np, int max_t, hipStream_t s, const char** where,
-                              const PassEvents* ev = nullptr);
+hipError_t launch_forward(BatchArgs& b, uint32_t grid_np, int max_t, bool empty_rows, hipStream_t s,
+                          const char** where, const PassEvents* ev = nullptr);
 hipError_t launch_backward(BatchArgs& b, uint32_t grid_np, int max_t, hipStream_t s, const char** where,
                               const PassEvents* ev = nullptr);
 hipError_t launch_palettize(BatchArgs& b, uint32_t grid_np, hipStream_t s, const char** where,

@@ -10,9 +10,9 @@
 //     merge per-workgroup results through dense partial rows instead of global
 //     atomics;
 //   * table-sized phases, bound by latency: the T softmax / centroid-update
-//     iterations and the unrolled analytic backward, one launch per iteration,
-//     64 workgroups per matrix, fixed-order tree reductions so the forward is
-//     bitwise repeatable;
+//     iterations and the unrolled analytic backward, one launch for all of
+//     them, up to 64 workgroups per matrix that exchange partial sums, summed
+//     in a fixed order so the forward is bitwise repeatable;
 //   * the dense comparison path (the same mathematics per weight over the
 //     N x k map) and the palettization export (packed nearest-entry indices).
 // Every launch carries up to MAXB = 28 matrices (blockIdx.y or a workgroup
@@ -49,21 +49,24 @@ __device__ __forceinline__ unsigned long long* stamp_row(int slot) {
     if (slot < 0 || slot >= STAMP_LAUNCHES || lin >= STAMP_BLOCKS) return nullptr;
     return stamp_ts + ((size_t)slot * STAMP_BLOCKS + lin) * STAMP_WORDS;
 }
-struct StampScope {   // words: 0 entry, 1 end, 2..6 phase marks, 7 XCC id
+// words: 0 entry, 1 end, 2..6 phase marks, 7 XCC id
+__device__ __forceinline__ void stamp_begin(int slot) {
+    unsigned long long* r = stamp_row(slot);
+    if (r && threadIdx.x == 0) {
+        r[0] = wall_clock64();
+        unsigned x;
+        asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(x));
+        r[7] = x;
+    }
+}
+__device__ __forceinline__ void stamp_end(int slot) {
+    unsigned long long* r = stamp_row(slot);
+    if (r && (threadIdx.x & 63) == 0) atomicMax(r + 1, wall_clock64());
+}
+struct StampScope {
     int slot;
-    __device__ explicit StampScope(int s) : slot(s) {
-        unsigned long long* r = stamp_row(slot);
-        if (r && threadIdx.x == 0) {
-            r[0] = wall_clock64();
-            unsigned x;
-            asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(x));
-            r[7] = x;
-        }
-    }
-    __device__ ~StampScope() {
-        unsigned long long* r = stamp_row(slot);
-        if (r && (threadIdx.x & 63) == 0) atomicMax(r + 1, wall_clock64());
-    }
+    __device__ explicit StampScope(int s) : slot(s) { stamp_begin(slot); }
+    __device__ ~StampScope() { stamp_end(slot); }
 };
 #define EDKM_STAMP_ENTRY(b) StampScope stamp_scope_((b).stamp_slot)
 #define EDKM_STAMP_MARK(b, i)                                                         \
@@ -81,7 +84,16 @@ static int stamp_next(const char* name) {
     return q;
 }
 #define EDKM_STAMP_SLOT(b, name) ((b).stamp_slot = stamp_next(name))
+// A launch that runs several steps has a record per step (`n` more records),
+// from the block holding the step's inputs to its having put its row, so that
+// the gap before a step of such a launch is the exchange of the rows.
+#define EDKM_STAMP_BEGIN(b, i) stamp_begin((b).stamp_slot + (i))
+#define EDKM_STAMP_END(b, i) stamp_end((b).stamp_slot + (i))
+#define EDKM_STAMP_MORE(name, n) do { for (int i_ = 0; i_ < (n); ++i_) (void)stamp_next(name); } while (0)
 #else
+#define EDKM_STAMP_BEGIN(b, i) ((void)0)
+#define EDKM_STAMP_END(b, i) ((void)0)
+#define EDKM_STAMP_MORE(name, n) ((void)0)
 #define EDKM_STAMP_ENTRY(b) ((void)0)
 #define EDKM_STAMP_MARK(b, i) ((void)0)
 #define EDKM_STAMP_SLOT(b, name) ((void)0)
@@ -122,28 +134,34 @@ __device__ __forceinline__ uint32_t to_half_bits(float x, int fmt) {
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-__device__ __forceinline__ float sgnf(float x) { return (float)((x > 0.f) - (x < 0.f)); }
+// y sgn(x), sgn(0) = 0
+__device__ __forceinline__ float mul_sgn(float y, float x) {
+    const float z = __uint_as_float(__float_as_uint(y) ^ (__float_as_uint(x) & 0x80000000u));
+    return x == 0.f ? 0.f : z;
+}
 
-// One attention row: a_j = softmax_j(-|v - c_j| / tau), with s2 = log2(e) / tau.
-// m is the nearest centroid; attn_row_sel also returns e[m] for a companion
-// array e.  The exponent -(|v - c_j| - |v - c_m|) / tau
+// One attention row: a_j = softmax_j(-|v - c_j| / tau), with s2 = log2(e) / tau,
+// up to the factor that attn_row_sel_un returns.  m is the nearest centroid;
+// em and fm receive e[m] and f[m] of companion arrays.  The exponent -(|v - c_j| - |v - c_m|) / tau
 // is formed without subtracting two distances of size |v|: when v lies on the
 // same side of c_j and c_m the difference is exactly |c_j - c_m|, otherwise v
 // lies between them and both distances are at most |c_j - c_m|.  (Subtracting
 // fp32 distances directly loses every digit once |v| is large against the
 // centroid spacing, e.g. an outlier far from the bulk.)
 template <int K>
-__device__ __forceinline__ void attn_row_sel(float v, const float (&c)[K], float s2, float (&a)[K],
-                                             const float (&e)[K], float& em) {
+__device__ __forceinline__ float attn_row_sel_un(float v, const float (&c)[K], float s2, float (&a)[K],
+                                                 const float (&e)[K], float& em, const float (&f)[K],
+                                                 float& fm) {
     float t[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) t[j] = v - c[j];
     // nearest centroid (first on ties), tracked by value: no run-time index
     float xm = fabsf(t[0]), cm = c[0], tm = t[0];
     em = e[0];
+    fm = f[0];
 #pragma unroll
     for (int j = 1; j < K; ++j) {
-        if (fabsf(t[j]) < xm) { xm = fabsf(t[j]); cm = c[j]; tm = t[j]; em = e[j]; }
+        if (fabsf(t[j]) < xm) { xm = fabsf(t[j]); cm = c[j]; tm = t[j]; em = e[j]; fm = f[j]; }
     }
     const uint32_t sm = __float_as_uint(tm) >> 31;
     float sum = 0.f;
@@ -154,15 +172,21 @@ __device__ __forceinline__ void attn_row_sel(float v, const float (&c)[K], float
         a[j] = __builtin_amdgcn_exp2f(-d * s2);
         sum += a[j];
     }
-    const float r = 1.0f / sum;
-#pragma unroll
-    for (int j = 0; j < K; ++j) a[j] *= r;
+    return 1.0f / sum;
 }
 
 template <int K>
-__device__ __forceinline__ void attn_row(float v, const float (&c)[K], float s2, float (&a)[K]) {
+__device__ __forceinline__ void attn_row_sel(float v, const float (&c)[K], float s2, float (&a)[K],
+                                             const float (&e)[K], float& em, const float (&f)[K], float& fm) {
+    const float r = attn_row_sel_un<K>(v, c, s2, a, e, em, f, fm);
+#pragma unroll
+    for (int j = 0; j < K; ++j) a[j] *= r;
+}
+template <int K>
+__device__ __forceinline__ void attn_row_sel(float v, const float (&c)[K], float s2, float (&a)[K],
+                                             const float (&e)[K], float& em) {
     float unused;
-    attn_row_sel<K>(v, c, s2, a, c, unused);
+    attn_row_sel<K>(v, c, s2, a, e, em, c, unused);
 }
 
 // Attention row of the dense comparison path.  The exponent is formed from
@@ -179,15 +203,17 @@ constexpr float DENSE_FAST_X = 256.f;
 // careful row, which normalises itself).
 template <int K>
 __device__ __forceinline__ float attn_row_dense_un(float v, const float (&c)[K], float s2, float (&a)[K],
-                                                   const float (&e)[K], float& em) {
+                                                   const float (&e)[K], float& em, const float (&f)[K],
+                                                   float& fm) {
     float d[K];
     d[0] = fabsf(v - c[0]);
     float xm = d[0];
     em = e[0];
+    fm = f[0];
 #pragma unroll
     for (int j = 1; j < K; ++j) {
         d[j] = fabsf(v - c[j]);
-        if (d[j] < xm) { xm = d[j]; em = e[j]; }
+        if (d[j] < xm) { xm = d[j]; em = e[j]; fm = f[j]; }
     }
     const float off = xm * s2;
     if (off <= DENSE_FAST_X) {
@@ -199,16 +225,22 @@ __device__ __forceinline__ float attn_row_dense_un(float v, const float (&c)[K],
         }
         return 1.0f / sum;
     }
-    attn_row_sel<K>(v, c, s2, a, e, em);
+    attn_row_sel<K>(v, c, s2, a, e, em, f, fm);
     return 1.0f;
 }
 
 template <int K>
 __device__ __forceinline__ void attn_row_dense(float v, const float (&c)[K], float s2, float (&a)[K],
-                                               const float (&e)[K], float& em) {
-    const float r = attn_row_dense_un<K>(v, c, s2, a, e, em);
+                                               const float (&e)[K], float& em, const float (&f)[K], float& fm) {
+    const float r = attn_row_dense_un<K>(v, c, s2, a, e, em, f, fm);
 #pragma unroll
     for (int j = 0; j < K; ++j) a[j] *= r;
+}
+template <int K>
+__device__ __forceinline__ void attn_row_dense(float v, const float (&c)[K], float s2, float (&a)[K],
+                                               const float (&e)[K], float& em) {
+    float unused;
+    attn_row_dense<K>(v, c, s2, a, e, em, c, unused);
 }
 
 // Deviations d_j = C^(T)_j - W~ of one map row a, W~ = sum_j a_j C^(T)_j,
@@ -231,24 +263,25 @@ __device__ __forceinline__ float centroid_dev(const float (&a)[K], const float (
 
 // Softmax-Jacobian deviations of one table row in the backward:
 //   dev_j = alpha_j - sum_i a_i alpha_i,  alpha_j = gS_j (v - c1_j),
-// written around the reference cm = c1_m (m the nearest centroid) as
-//   dev_j = (gS_j - gbar)(v - cm) - (gS_j (c1_j - cm) - hb),
-//   gbar = sum_i a_i gS_i,  hb = sum_i a_i gS_i (c1_i - cm),
-// which never subtracts two terms of size |v|.  Returns gbar.
+// written around the reference cm = c1_m, gm = gS_m (m the nearest centroid) as
+//   dev_j = (gS_j - gm - db)(v - cm) - (gS_j (c1_j - cm) - hb),
+//   db = sum_i a_i (gS_i - gm),  hb = sum_i a_i gS_i (c1_i - cm),
+// which subtracts neither two terms of size |v| nor, for a nearly one-hot row,
+// two nearly equal gS (their rounding error, times |v| / tau, was dL/dw's
+// largest for weights far from zero).  Returns sum_i a_i gS_i = gm + db.
 template <int K>
 __device__ __forceinline__ float softmax_dev(float v, const float (&a)[K], const float (&gS)[K],
-                                             const float (&c1)[K], float cm, float (&dev)[K]) {
-    float gbar = 0.f, hb = 0.f;
+                                             const float (&c1)[K], float cm, float gm, float (&dev)[K]) {
+    float db = 0.f, hb = 0.f;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        const float ag = a[j] * gS[j];
-        gbar += ag;
-        hb = fmaf(ag, c1[j] - cm, hb);
+        db = fmaf(a[j], gS[j] - gm, db);
+        hb = fmaf(a[j] * gS[j], c1[j] - cm, hb);
     }
     const float w1 = v - cm;
 #pragma unroll
-    for (int j = 0; j < K; ++j) dev[j] = fmaf(gS[j] - gbar, w1, -fmaf(gS[j], c1[j] - cm, -hb));
-    return gbar;
+    for (int j = 0; j < K; ++j) dev[j] = fmaf((gS[j] - gm) - db, w1, -fmaf(gS[j], c1[j] - cm, -hb));
+    return gm + db;
 }
 
 // DPP lane moves: a VALU operand read from another lane of the same row of 16
@@ -414,60 +447,88 @@ __device__ __forceinline__ float tree_sum(float (&x)[N]) {
     return x[0];
 }
 
-// Column totals of a table partial block (T_WG rows, PSTRIDE floats apart), in
-// a fixed tree order and with every load issued up front: virtual column c of
-// NC (a power of two, 4 <= NC <= T_THREADS) is read from src(c), a pointer to
-// its row 0 (null: a column not read).  Thread t holds rows [R s, R s + R) of
-// column c = t % NC, s = t / NC, R = T_WG NC / T_THREADS; stage() sums them
-// pairwise into red[t] (T_THREADS floats of LDS) and synchronises the block;
-// total(red, c) then sums the T_THREADS / NC segment sums of column c
-// pairwise.  (Wave reductions per column had each cost a chain of dependent
-// lane moves, and a kernel read its partial block only after its flags: two
-// round trips to memory and about 2 us per table launch.)
+// Sum over the lanes of a wave (all active) with the same lane % NC, 2 <= NC <=
+// 32, in every lane: rotations within a row of 16 lanes, then the swaps of
+// odd with even rows and of the wave's halves (each returns both operands of
+// the sum).  The association order is fixed per lane.
+constexpr int DPP_ROR2 = 0x122, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128;   // lane i <- lane i - n of its row, cyclic
 template <int NC>
-struct PartCols {
-    static_assert(NC >= 4 && NC <= T_THREADS && (NC & (NC - 1)) == 0, "NC: a power of two in [4, T_THREADS]");
+__device__ __forceinline__ float wave_cols(float x) {
+    static_assert(NC >= 2 && NC <= 32 && (NC & (NC - 1)) == 0, "NC: a power of two in [2, 32]");
+    if constexpr (NC <= 2) x += dpp_f<DPP_ROR2>(x, x);
+    if constexpr (NC <= 4) x += dpp_f<DPP_ROR4>(x, x);
+    if constexpr (NC <= 8) x += dpp_f<DPP_ROR8>(x, x);
+    if constexpr (NC <= 16) {
+        const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    }
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+
+// The same in double precision.
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double x) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+    return __longlong_as_double((long long)dpp_u64<CTRL>(u, u));
+}
+template <int NC>
+__device__ __forceinline__ double wave_cols(double x) {
+    auto both = [](const auto& lo, const auto& hi) {
+        auto d = [](uint32_t h, uint32_t l) { return __longlong_as_double((long long)(((unsigned long long)h << 32) | l)); };
+        return d(hi[0], lo[0]) + d(hi[1], lo[1]);
+    };
+    if constexpr (NC <= 4) x += dpp_d<DPP_ROR4>(x);
+    if constexpr (NC <= 8) x += dpp_d<DPP_ROR8>(x);
+    if constexpr (NC <= 16) {
+        const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+        const uint32_t l = (uint32_t)u, h = (uint32_t)(u >> 32);
+        x = both(__builtin_amdgcn_permlane16_swap(l, l, false, false), __builtin_amdgcn_permlane16_swap(h, h, false, false));
+    }
+    const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+    const uint32_t l = (uint32_t)u, h = (uint32_t)(u >> 32);
+    return both(__builtin_amdgcn_permlane32_swap(l, l, false, false), __builtin_amdgcn_permlane32_swap(h, h, false, false));
+}
+
+// Column totals of T_WG rows of NC values, in a fixed order and in double
+// precision (the virtual blocks' fp32 sums carry independent roundings of
+// their own size; adding them in fp32 as well would round at the size of the
+// total, which made up most of C^(t)'s error): thread t holds rows [R s, R s + R)
+// of column c = t % NC, s = t / NC, R = T_WG NC / T_THREADS; stage() sums over
+// each wave's lanes of a column and leaves the waves' sums in red (4 NC
+// doubles of LDS) -- the caller synchronises the block -- and total(red, c)
+// adds those.  (One thread per column adding the T_THREADS / NC segment sums
+// from LDS had cost up to 64 LDS reads and as many registers.)
+template <int NC>
+struct Cols {
     static constexpr int SEGS = T_THREADS / NC;
     static constexpr int R = T_WG / SEGS;
     static_assert(R >= 1, "at least one row per thread");
-    float x[R];
-    template <class Src>
-    __device__ __forceinline__ void load(Src src) {
-        const int c = threadIdx.x % NC, sg = threadIdx.x / NC;
-        const float* p = src(c);
+    __device__ __forceinline__ static void stage(const float (&x)[R], double* red) {
+        double y = x[0];
 #pragma unroll
-        for (int r = 0; r < R; ++r) x[r] = p ? p[(size_t)(sg * R + r) * PSTRIDE] : 0.f;
+        for (int r = 1; r < R; ++r) y += x[r];
+        y = wave_cols<NC>(y);
+        const int lane = threadIdx.x & 63;
+        if (lane < NC) red[(threadIdx.x >> 6) * NC + lane] = y;
     }
-    // column c of the block at base (no null test, so no branch among the loads)
-    __device__ __forceinline__ void load_block(const float* base) {
-        const int c = threadIdx.x % NC, sg = threadIdx.x / NC;
-        const float* p = base + c;
-#pragma unroll
-        for (int r = 0; r < R; ++r) x[r] = p[(size_t)(sg * R + r) * PSTRIDE];
-    }
-    __device__ __forceinline__ void stage(float* red) {
-        red[threadIdx.x] = tree_sum<R>(x);
-        __syncthreads();
-    }
-    __device__ __forceinline__ static float total(const float* red, int c) {
-        float y[SEGS];
-#pragma unroll
-        for (int sg = 0; sg < SEGS; ++sg) y[sg] = red[sg * NC + c];
-        return tree_sum<SEGS>(y);
+    __device__ __forceinline__ static double total(const double* red, int c) {
+        static_assert(T_THREADS == 256, "four waves");
+        return (red[c] + red[NC + c]) + (red[2 * NC + c] + red[3 * NC + c]);
     }
 };
 
-// Sum of NV per-thread values (NV a power of two dividing T_THREADS) over a
-// T_THREADS block, in a fixed tree order: thread NV s + j sums value j of
-// threads NV s .. NV s + NV - 1 pairwise, then thread j sums the T_THREADS /
-// NV segment sums pairwise.  Returns the total of value threadIdx.x in threads
-// [0, NV).  red: BLOCK_TOTAL_LDS(NV) floats of LDS; every thread
-// calls it.  (One dependent chain of lane moves per value had cost 0.8-2.5 us
-// per table kernel.)
-#define BLOCK_TOTAL_LDS(NV) (T_THREADS * ((NV) + 1) + T_THREADS)
+// Sum of NV per-thread values (NV a power of two in [2, 32]) over a T_THREADS
+// block, in a fixed tree order: thread NV s + j sums value j of threads
+// NV s .. NV s + NV - 1 pairwise, then each wave its lanes of a value
+// (wave_cols), then thread j the waves' sums.  Returns the total of value
+// threadIdx.x in threads [0, NV), 0 in the others.  red: BLOCK_TOTAL_LDS(NV)
+// floats of LDS; every thread calls it.  (One dependent chain of lane moves
+// per value had cost 0.8-2.5 us per table kernel.)
+#define BLOCK_TOTAL_LDS(NV) (T_THREADS * ((NV) + 1) + T_THREADS / 64 * (NV))
 template <int NV>
 __device__ __forceinline__ float block_total(const float (&v)[NV], float* red) {
-    static_assert(NV <= T_THREADS && T_THREADS % NV == 0, "NV divides the block");
+    static_assert(T_THREADS == 256, "four waves");
     constexpr int LD = NV + 1;   // odd pitch: a value's rows fall in different banks
     float* seg = red + T_THREADS * LD;
 #pragma unroll
@@ -477,16 +538,12 @@ __device__ __forceinline__ float block_total(const float (&v)[NV], float* red) {
     float a[NV];
 #pragma unroll
     for (int i = 0; i < NV; ++i) a[i] = red[(sg * NV + i) * LD + j];
-    seg[threadIdx.x] = tree_sum<NV>(a);
+    const float y = wave_cols<NV>(tree_sum<NV>(a));
+    const int lane = threadIdx.x & 63;
+    if (lane < NV) seg[(threadIdx.x >> 6) * NV + lane] = y;
     __syncthreads();
-    float tot = 0.f;
-    if (threadIdx.x < NV) {
-        float y[T_THREADS / NV];
-#pragma unroll
-        for (int q = 0; q < T_THREADS / NV; ++q) y[q] = seg[q * NV + threadIdx.x];
-        tot = tree_sum<T_THREADS / NV>(y);
-    }
-    return tot;
+    if (threadIdx.x >= NV) return 0.f;
+    return (seg[j] + seg[NV + j]) + (seg[2 * NV + j] + seg[3 * NV + j]);
 }
 
 // Matrix of an N-pass workgroup, and its slice [beg, end).
@@ -697,6 +754,10 @@ __device__ __forceinline__ void st_u4_nt(void* p, uint4 x) {
     __builtin_nontemporal_store(v4u_t{x.x, x.y, x.z, x.w}, reinterpret_cast<v4u_t*>(p));
 }
 
+// Words of the table phases' exchange rows before a value arrives (see the
+// table phases): a NaN that xw_put never stores.
+constexpr uint32_t XW_EMPTY = 0xFFFFFFFFu;
+
 // ----------------------------------------------------------------------------
 // init_unique: zero, histogram, partial merge, window selection
 
@@ -706,6 +767,8 @@ __global__ void __launch_bounds__(T_THREADS) k_init_zero(BatchArgs b) {
     const Ws ws = carve_workspace(M.wsb, M.max_iter);
     for (int u = blockIdx.x * T_THREADS + threadIdx.x; u < NKEYS; u += gridDim.x * T_THREADS)
         ws.counts[u] = 0u;
+    for (int i = blockIdx.x * T_THREADS + threadIdx.x; i < M.max_iter * T_WG * 2 * M.k; i += gridDim.x * T_THREADS)
+        ws.fx[i] = XW_EMPTY;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         DevState* st = ws.st;
         st->teff = 0;
@@ -713,6 +776,16 @@ __global__ void __launch_bounds__(T_THREADS) k_init_zero(BatchArgs b) {
         st->nonfinite = 0u;
         st->num_unique = 0u;
     }
+}
+
+// Empties the forward's exchange rows, for a forward after one that failed
+// between its launches.
+__global__ void __launch_bounds__(T_THREADS) k_empty_rows(BatchArgs b) {
+    EDKM_STAMP_ENTRY(b);
+    const MatArgs& M = b.m[blockIdx.y];
+    const Ws ws = carve_workspace(M.wsb, M.max_iter);
+    for (int i = blockIdx.x * T_THREADS + threadIdx.x; i < M.max_iter * T_WG * 2 * M.k; i += gridDim.x * T_THREADS)
+        ws.fx[i] = XW_EMPTY;
 }
 
 // Pattern histogram.  Magnitudes [0, W4) of both signs (|w| < 16) count in
@@ -1005,185 +1078,241 @@ __global__ void __launch_bounds__(NP_THREADS) k_window(BatchArgs b) {
 }
 
 // ----------------------------------------------------------------------------
-// forward table phase
+// table phases: one launch each, exchanging partial sums between its blocks
+//
+// The 65,536 patterns are dealt to T_WG virtual blocks of T_THREADS threads; a
+// physical block runs VB of them in turn, so a matrix takes T_WG / VB blocks.
+// An iteration needs the sums of all T_WG partial rows before the next one can
+// start.  The rows are exchanged inside the launch: each virtual block stores
+// its row with relaxed agent-scope stores and every block polls all rows until
+// none holds XW_EMPTY, so a word is its own arrival flag and no fence, counter
+// or cache write-back is involved.  A round of this takes 1.1 us for one
+// matrix and 1.8 us for seven (a probe), against 4-6 us for a dependent launch
+// with its drain, its dispatch and its argument and count loads.  Kernel times
+// of the launches one phase took before -> of its one launch now: 4096x4096
+// at 3 bits, forward 23.1 -> 18.4 us, backward 24.2 -> 19.6 us; decoder layer
+// 28.2 -> 22.3 and 27.3 -> 25.1 us; an early stop among 30 iterations at 4
+// bits 123 -> 81 us.  What is left of a round is the stores reaching memory
+// and the loads coming back.  (A grid barrier with release and acquire had
+// cost 10 us and more: it writes back and invalidates the XCDs' L2s.)
+//
+// No block relies on another one running.  A block that has waited XW_WAIT
+// computes the rows it still misses itself, with the same code and therefore
+// the same bits, so every wait ends whatever else occupies the GPU; a block
+// that starts late finds the rows it needs already there.
+//
+// Every row word is XW_EMPTY when a phase starts: the forward's rows are
+// emptied by k_init_zero and again by k_gather_wt, the launch after the phase
+// (a forward may be repeated after one init_unique); the backward's by
+// k_keyed_grad, two launches before it.
 
-// Table keys of a thread: T_KPT per thread over T_WG blocks x T_THREADS threads
-// (= 65,536).  Kernels load everything the 4 patterns need first and compute
-// afterwards, so the loads overlap instead of forming a chain.
-__device__ __forceinline__ int table_key(int r) {
-    return blockIdx.x * T_THREADS + threadIdx.x + r * (T_WG * T_THREADS);
+#ifndef EDKM_XW_WAIT
+#define EDKM_XW_WAIT 2000
+#endif
+constexpr long long XW_WAIT = EDKM_XW_WAIT;  // wall-clock ticks (100 MHz): 20 us
+
+// Blocks of one launch, at most: as many as the GPU's 256 CUs hold at a time, 4
+// a CU (128 registers a thread), or 3 or 2 where the backward at k = 16 needs
+// more; the kernels' launch bounds keep to that, so that on an idle GPU no block
+// waits for one that has not started.
+template <int K, int NVB, bool BWD>
+constexpr int TABLE_BLOCKS = K == 16 && BWD ? (NVB == 1 ? 768 : 512) : 1024;
+
+// A value that is the same in every lane, moved to a scalar register.
+__device__ __forceinline__ float uniform(float x) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
 
-// Iteration t (1..max_iter): C^(t-1) from the partials of iteration t-1 (or
-// c_in), early stop test, then this block's partial S_j = sum n_u a_uj and
-// P_j = sum n_u a_uj v_u.  Grid (T_WG, count).
-template <int K>
-__global__ void __launch_bounds__(T_THREADS) k_fwd_iter(BatchArgs b) {
-    EDKM_STAMP_ENTRY(b);
-    __shared__ float red[BLOCK_TOTAL_LDS(2 * K)];
-    __shared__ float csh[K];
-    __shared__ int stop;
-    const MatArgs& M = b.m[blockIdx.y];
-    const int t = b.t;
-    // Every load first, with no branch in between (a branch or an early
-    // return between them had the compiler wait for each scalar load before
-    // issuing the next, 2-3 round trips): the pattern counts, the previous
-    // iteration's partial block and C^(t-2) (at t = 1: c_in, and partial row 0,
-    // unused), the convergence flag.  Indices are clamped for launches past
-    // this matrix's max_iter, which return below.
-    const float* c_in = M.c_in;
-    const int max_iter = M.max_iter, fmt = M.fmt;
-    const float eps = b.eps, s2 = b.s2;
-    // the arguments, in one wait
-    asm volatile("" ::"s"(c_in), "s"(max_iter), "s"(fmt), "s"(t), "s"(eps), "s"(s2), "s"(M.wsb));
-    const Ws ws = carve_workspace(M.wsb, M.max_iter);
-    const int tl = max(1, min(t, max_iter));
-    uint32_t n4[T_KPT];
-#pragma unroll
-    for (int r = 0; r < T_KPT; ++r) n4[r] = ws.counts[table_key(r)];
-    PartCols<2 * K> pc;
-    pc.load_block(ws.tpart + (size_t)(tl - 1) * T_WG * PSTRIDE);
-    const float* cp = tl > 1 ? ws.chist + (tl - 2) * KMAX : c_in;
-    const float cprev = cp[threadIdx.x % K];
-    DevState* st = ws.st;
-    const int conv = st->conv;
-    EDKM_STAMP_MARK(b, 2);   // loads issued
-    if (t > max_iter) return;
-    const bool lead = blockIdx.x == 0;
-    if (t == 1) {
-        if (threadIdx.x < K) {
-            csh[threadIdx.x] = cprev;
-            if (lead) { ws.chist[threadIdx.x] = cprev; ws.shist[threadIdx.x] = 0.f; }
-        }
-        if (lead && threadIdx.x == 0) { st->conv = 0; st->teff = 0; }
-        __syncthreads();
-    } else {
-        if (threadIdx.x == 0) stop = 0;
-        pc.stage(red);
-        if (conv) return;
-        if (threadIdx.x < K) {
-            const int j = threadIdx.x;
-            const float S = PartCols<2 * K>::total(red, j), P = PartCols<2 * K>::total(red, K + j);
-            const float cn = S > 0.f ? P / S : cprev;
-            csh[j] = cn;
-            if (lead) { ws.chist[(t - 1) * KMAX + j] = cn; ws.shist[(t - 1) * KMAX + j] = S; }
-            if (eps > 0.f && !(fabsf(cn - cprev) <= eps)) atomicOr(&stop, 1);
-        }
-        __syncthreads();
-        if (eps > 0.f && stop == 0) {   // max_j |C^(t-1) - C^(t-2)| <= eps: T = t - 1
-            if (lead && threadIdx.x == 0) { st->teff = t - 1; st->conv = 1; }
-            return;
-        }
-    }
-    EDKM_STAMP_MARK(b, 3);   // partial block summed, C formed
-    float c[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) c[j] = csh[j];
-    float acc[2 * K];
-#pragma unroll
-    for (int j = 0; j < 2 * K; ++j) acc[j] = 0.f;
-#pragma unroll
-    for (int r = 0; r < T_KPT; ++r) {
-        const int u = table_key(r);
-        const uint32_t n = n4[r];
-        if (n == 0u || !key_finite(u, fmt)) continue;
-        const float v = key_value(u, fmt);
-        float a[K];
-        attn_row<K>(v, c, s2, a);
-        const float nf = (float)n;
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-            const float w = nf * a[j];
-            acc[j] += w;
-            acc[K + j] = fmaf(w, v, acc[K + j]);
-        }
-    }
-    EDKM_STAMP_MARK(b, 4);   // patterns done
-    const float tot = block_total<2 * K>(acc, red);
-    EDKM_STAMP_MARK(b, 5);   // block summed
-    if (threadIdx.x < 2 * K) ws.tpart[((size_t)t * T_WG + blockIdx.x) * PSTRIDE + threadIdx.x] = tot;
+__device__ __forceinline__ void xw_put(uint32_t* p, float x) {
+    uint32_t v = __float_as_uint(x);
+    if (v == XW_EMPTY) v = 0x7FC00000u;      // a NaN either way
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t xw_get(const uint32_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// After the last iteration: C^(T), c_out, T; per occupied pattern the W~ value
+// The T_WG rows of NC words of one round, summed by column as in Cols.  Row q is
+// kept at place (q % R) SEGS + q / R, so that each of a wave's loads reads
+// contiguous words.
+template <int NC>
+struct Rows {
+    static constexpr int SEGS = Cols<NC>::SEGS, R = Cols<NC>::R;
+    uint32_t* base;
+    __device__ __forceinline__ uint32_t* word(int q, int c) const { return base + ((q % R) * SEGS + q / R) * NC + c; }
+    __device__ __forceinline__ void put(int q, float x) const {   // thread c < NC holds column c's value
+        if (threadIdx.x < NC) xw_put(word(q, threadIdx.x), x);
+    }
+    // Waits for every row and leaves the waves' column sums in red (Cols), block
+    // synchronised.  miss: an LDS word that no earlier round set
+    // to `round` or above; round is advanced.  help(q) computes and puts row q
+    // (all threads).
+    template <class Help>
+    __device__ __forceinline__ void gather(double* red, int* miss, int& round, Help help) const {
+        const uint32_t* p = base + (threadIdx.x / NC) * NC + threadIdx.x % NC;
+        for (;;) {
+            float x[R];
+            bool ok = false;
+            for (long long t0 = -1;;) {
+                uint32_t w[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) w[r] = xw_get(p + r * SEGS * NC);
+                ok = true;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    ok = ok && w[r] != XW_EMPTY;
+                    x[r] = __uint_as_float(w[r]);
+                }
+                if (ok) break;
+                const long long now = wall_clock64();
+                if (t0 < 0) t0 = now;
+                else if (now - t0 > XW_WAIT) break;
+            }
+            ++round;
+            Cols<NC>::stage(x, red);
+            if (!ok) *miss = round;
+            __syncthreads();
+            if (*miss != round) return;
+            for (int q = 0; q < T_WG; ++q)
+                if (__syncthreads_or(threadIdx.x < NC && xw_get(word(q, threadIdx.x)) == XW_EMPTY)) help(q);
+        }
+    }
+};
+
+// Pattern r of this thread in virtual block q.  A thread's r and r + 2 are one
+// magnitude's two signs and a virtual block's patterns are neighbours, so that
+// the first sums of the tree cancel most of P_j where the weights lie around
+// zero.  (Runs of 64 patterns dealt round-robin balance the virtual blocks
+// better, but left C^(T) with three times the rounding error at tau = 0.05,
+// where every centroid moves to the weights' mean.)
+__device__ __forceinline__ uint32_t table_key(int q, int r) {
+    return (uint32_t)(q * T_THREADS + r * (T_WG * T_THREADS)) + threadIdx.x;
+}
+
+// The forward's table phase.  Iterations t = 1..T: the rows hold, per virtual
+// block, S_j = sum n_u a_uj and P_j = sum n_u a_uj v_u with the map of C^(t-1);
+// every block forms C^(t)_j = P_j / S_j from all of them and applies the early
+// stop.  Then per occupied pattern the W~ value
 // Tab_u = sum_j a^(T)_uj C^(T)_j (a^(T) built from C^(T-1)) and
 // H_u = -(1/tau) sum_j a^(T)_uj (C^(T)_j - Tab_u) sgn(v_u - C^(T-1)_j);
-// clears G.  Grid (T_WG, count).
-template <int K>
-__global__ void __launch_bounds__(T_THREADS) k_fwd_out(BatchArgs b) {
-    EDKM_STAMP_ENTRY(b);
-    __shared__ float red[T_THREADS];
-    __shared__ float cT[K], cP[K];
+// clears G.  Grid (T_WG / VB, count).
+template <int K, int VB>
+__global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, false> / 256)) k_fwd_table(BatchArgs b) {
+    __shared__ float red[BLOCK_TOTAL_LDS(2 * K)];
+    __shared__ double cols[8 * K];
+    __shared__ float c1sh[K], c0sh[K];   // C^(t), C^(t-1)
+    __shared__ int stop, miss;
     const MatArgs& M = b.m[blockIdx.y];
-    // the arguments, in one wait (read where they are used, each had cost a
-    // round trip of its own)
-    const int max_iter = M.max_iter, fmt = M.fmt;
+    const float* c_in = M.c_in;
     float* const c_out = M.c_out;
     int32_t* const iters_out = M.iters_out;
-    const float s2 = b.s2, inv_tau = b.inv_tau;
-    asm volatile("" ::"s"(max_iter), "s"(fmt), "s"(c_out), "s"(iters_out), "s"(s2), "s"(inv_tau), "s"(M.wsb));
+    const int max_iter = M.max_iter, fmt = M.fmt;
+    const float eps = b.eps, s2 = b.s2, inv_tau = b.inv_tau;
+    // the arguments, in one wait
+    asm volatile("" ::"s"(c_in), "s"(c_out), "s"(iters_out), "s"(max_iter), "s"(fmt), "s"(eps), "s"(s2),
+                 "s"(inv_tau), "s"(M.wsb));
     const Ws ws = carve_workspace(M.wsb, M.max_iter);
-    // every load first (the partial block and C^(T-1) of a run that did all
-    // max_iter iterations, the convergence state; an early stop reads its two
-    // rows afterwards)
-    DevState* st = ws.st;
-    const int conv = st->conv, teff = st->teff;
-    uint32_t n4[T_KPT];
-#pragma unroll
-    for (int r = 0; r < T_KPT; ++r) n4[r] = ws.counts[table_key(r)];
-    PartCols<2 * K> pc;
-    pc.load_block(ws.tpart + (size_t)max_iter * T_WG * PSTRIDE);
-    const float cprev = ws.chist[(max_iter - 1) * KMAX + threadIdx.x % K];
     const bool lead = blockIdx.x == 0;
-    pc.stage(red);
-    int T;
-    if (conv) {
-        T = teff;
-        if (threadIdx.x < K) {
-            cT[threadIdx.x] = ws.chist[T * KMAX + threadIdx.x];
-            cP[threadIdx.x] = ws.chist[(T - 1) * KMAX + threadIdx.x];
-        }
-        __syncthreads();
-    } else {
-        T = max_iter;
+    auto vq = [&](int v) { return (int)blockIdx.x + v * (T_WG / VB); };   // virtual block v of this block
+    uint32_t nv[VB][T_KPT];   // counts, in registers for the whole launch
+    auto counts = [&](int q, uint32_t (&n)[T_KPT]) {
+#pragma unroll
+        for (int r = 0; r < T_KPT; ++r) n[r] = ws.counts[table_key(q, r)];
+    };
+#pragma unroll
+    for (int v = 0; v < VB; ++v) counts(vq(v), nv[v]);
+    if (threadIdx.x < K) {
+        const float c = c_in[threadIdx.x];
+        c1sh[threadIdx.x] = c;
+        if (lead) { ws.chist[threadIdx.x] = c; ws.shist[threadIdx.x] = 0.f; }
+    }
+    if (threadIdx.x == 0) { stop = 0; miss = 0; }
+    __syncthreads();
+    int T = 0, round = 0;
+    for (;;) {
+        ++T;
+        EDKM_STAMP_BEGIN(b, T - 1);
+        float c[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) c[j] = uniform(c1sh[j]);
+        // row q's totals, in threads [0, 2K)
+        auto partial = [&](int q, const uint32_t (&n)[T_KPT]) {
+            float acc[2 * K];
+#pragma unroll
+            for (int j = 0; j < 2 * K; ++j) acc[j] = 0.f;
+#pragma unroll
+            for (int r = 0; r < T_KPT; ++r) {
+                const uint32_t u = table_key(q, r);
+                if (n[r] == 0u || !key_finite(u, fmt)) continue;
+                const float v = key_value(u, fmt);
+                float a[K], unused;
+                const float nr = (float)n[r] * attn_row_sel_un<K>(v, c, s2, a, c, unused, c, unused);
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    const float w = nr * a[j];
+                    acc[j] += w;
+                    acc[K + j] = fmaf(w, v, acc[K + j]);
+                }
+            }
+            return block_total<2 * K>(acc, red);
+        };
+        const Rows<2 * K> rows{ws.fx + (size_t)(T - 1) * T_WG * 2 * K};
+#pragma unroll
+        for (int v = 0; v < VB; ++v) rows.put(vq(v), partial(vq(v), nv[v]));
+        EDKM_STAMP_END(b, T - 1);
+        rows.gather(cols, &miss, round, [&](int q) {
+            uint32_t n[T_KPT];
+            counts(q, n);
+            rows.put(q, partial(q, n));
+        });
         if (threadIdx.x < K) {
             const int j = threadIdx.x;
-            const float S = PartCols<2 * K>::total(red, j), P = PartCols<2 * K>::total(red, K + j);
-            const float cn = S > 0.f ? P / S : cprev;
-            cT[j] = cn;
-            cP[j] = cprev;
-            if (lead) { ws.chist[T * KMAX + j] = cn; ws.shist[T * KMAX + j] = S; }
+            const double S = Cols<2 * K>::total(cols, j), P = Cols<2 * K>::total(cols, K + j);
+            const float cprev = c1sh[j], cn = S > 0.0 ? (float)(P / S) : cprev;
+            c0sh[j] = cprev;
+            c1sh[j] = cn;
+            if (lead) { ws.chist[T * KMAX + j] = cn; ws.shist[T * KMAX + j] = (float)S; }
+            if (!(fabsf(cn - cprev) <= eps)) stop = T;
         }
-        if (lead && threadIdx.x == 0) st->teff = T;
         __syncthreads();
+        // max_j |C^(T) - C^(T-1)| <= eps ends the iteration
+        if (T == max_iter || (eps > 0.f && stop != T)) break;
     }
+    EDKM_STAMP_BEGIN(b, b.t);
     if (lead) {
         if (threadIdx.x < K) {
-            c_out[threadIdx.x] = cT[threadIdx.x];
-            ws.cfin[threadIdx.x] = cP[threadIdx.x];          // for k_grad_top, which does not know T
-            ws.cfin[KMAX + threadIdx.x] = cT[threadIdx.x];
+            c_out[threadIdx.x] = c1sh[threadIdx.x];
+            ws.cfin[threadIdx.x] = c0sh[threadIdx.x];        // for k_grad_top, which does not know T
+            ws.cfin[KMAX + threadIdx.x] = c1sh[threadIdx.x];
         }
-        if (threadIdx.x == 0 && iters_out) *iters_out = T;
+        if (threadIdx.x == 0) {
+            ws.st->teff = T;
+            if (iters_out) *iters_out = T;
+        }
     }
     float c1[K], c0[K];
 #pragma unroll
-    for (int j = 0; j < K; ++j) { c1[j] = cT[j]; c0[j] = cP[j]; }
+    for (int j = 0; j < K; ++j) { c1[j] = c1sh[j]; c0[j] = c0sh[j]; }
 #pragma unroll
-    for (int r = 0; r < T_KPT; ++r) {
-        const int u = table_key(r);
-        ws.G[u] = 0.f;
-        const uint32_t n = n4[r];
-        if (n == 0u) continue;
-        if (!key_finite(u, fmt)) { ws.tab[u] = __builtin_nanf(""); ws.H[u] = __builtin_nanf(""); continue; }
-        const float v = key_value(u, fmt);
-        float a[K], d[K], c1m;
-        attn_row_sel<K>(v, c0, s2, a, c1, c1m);
-        const float tv = centroid_dev<K>(a, c1, c1m, d);
-        float h = 0.f;
+    for (int v = 0; v < VB; ++v) {
 #pragma unroll
-        for (int j = 0; j < K; ++j) h = fmaf(a[j] * d[j], sgnf(v - c0[j]), h);
-        ws.tab[u] = tv;
-        ws.H[u] = -h * inv_tau;
+        for (int r = 0; r < T_KPT; ++r) {
+            const uint32_t u = table_key(vq(v), r);
+            ws.G[u] = 0.f;
+            if (nv[v][r] == 0u) continue;
+            if (!key_finite(u, fmt)) { ws.tab[u] = __builtin_nanf(""); ws.HR[u].x = __builtin_nanf(""); continue; }
+            const float x = key_value(u, fmt);
+            float a[K], d[K], c1m;
+            attn_row_sel<K>(x, c0, s2, a, c1, c1m);
+            const float tv = centroid_dev<K>(a, c1, c1m, d);
+            float h = 0.f;
+#pragma unroll
+            for (int j = 0; j < K; ++j) h += mul_sgn(a[j] * d[j], x - c0[j]);
+            ws.tab[u] = tv;
+            ws.HR[u].x = -h * inv_tau;
+        }
     }
+    EDKM_STAMP_END(b, b.t);
 }
 
 // ----------------------------------------------------------------------------
@@ -1199,6 +1328,10 @@ __global__ void __launch_bounds__(NP_THREADS) k_gather_wt(BatchArgs b) {
     const uint32_t wl = blockIdx.x - b.wg_begin[mi];
     const int lo = ws.st->lo4, w = ws.st->w4;
     const float* tab = ws.tab;
+    // the table phase is over: empty its rows for another forward
+    for (uint32_t i = wl * NP_THREADS + threadIdx.x; i < (uint32_t)(M.max_iter * T_WG * 2 * M.k);
+         i += M.wg_count * NP_THREADS)
+        ws.fx[i] = XW_EMPTY;
     fill_lds<2 * W4, NP_THREADS>(tw, tab, 2 * w, [&](int i) {
         const int s = i >= w;
         return (s << 15) | (lo + i - s * w);
@@ -1316,10 +1449,11 @@ __global__ void __launch_bounds__(NP_THREADS) k_keyed_grad(BatchArgs b) {
         for (int i = threadIdx.x; i < n16; i += NP_THREADS) reinterpret_cast<uint4*>(lds)[i] = uint4{0u, 0u, 0u, 0u};
     }
     if (threadIdx.x == 0) { emax_sh = 0; esum_sh = 0; ecnt_sh = 0; }
-    // Clear the backward's first partial block, which k_grad_top adds into
-    // next; the previous backward's reads of it are over.
-    for (uint32_t i = wl * NP_THREADS + threadIdx.x; i < (uint32_t)(T_WG * PSTRIDE); i += M.wg_count * NP_THREADS)
-        ws.bpart[i] = 0.f;
+    // Empty the rows that the backward's table phase exchanges; the previous
+    // backward's reads of them are over.
+    for (uint32_t i = wl * NP_THREADS + threadIdx.x; i < (uint32_t)(T_WG * (M.max_iter * max(M.k, 4) + 2 * M.k));
+         i += M.wg_count * NP_THREADS)
+        ws.bx[i] = XW_EMPTY;
     __syncthreads();
     {   // sample: 64 consecutive values per wave, the waves' runs spread over the
         // matrix (one value per thread at scattered indices had cost a 128-byte
@@ -1462,14 +1596,11 @@ __global__ void __launch_bounds__(NP_THREADS) k_gather_grad(BatchArgs b) {
         // dL/dC^(0) = (1/tau) sum of the t = 1 partials + the terms that bypass
         // the softmax; wave j takes centroid j (one wave doing all k had held
         // this workgroup back by about 3 us, and with it the whole pass)
-        const int T = st->teff, k = M.k, j = threadIdx.x >> 6, lane = threadIdx.x & 63;
-        const float* p1 = ws.bpart + (size_t)1 * T_WG * PSTRIDE;
-        const float* p0 = ws.bpart;
-        const float x = wave_sum(tpart_rows(p1, lane, j));
-        const float e = wave_sum(tpart_rows(p0, lane, k + j));
+        const int T = st->teff, j = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        const float x = wave_sum(tpart_rows(ws.bpart, lane, j));
         if (lane == 0) {
             float gc = x * b.inv_tau;
-            if (T == 1) gc += e * b.inv_tau;
+            if (T == 1) gc += ws.ehist[j] * b.inv_tau;
             if (!(ws.shist[KMAX + j] > 0.f)) gc += ws.ghist[KMAX + j];
             M.gc[j] = gc;
         }
@@ -1789,11 +1920,14 @@ __global__ void __launch_bounds__(NP_THREADS) k_inverse(BatchArgs b) {
 // adds that partial sum times the pattern's terms.  The last blockIdx.y takes
 // what the keyed-sum pass added to the global G instead (patterns outside the
 // window, values above its fixed-point limit, wrap corrections), over all
-// 65,536 patterns.  Block totals are added with float atomics into the 64 rows
-// of the backward's first partial block, which k_keyed_grad clears.
-// (Summing the rows into G first, then
-// a table kernel over G, took one launch more.)  Grid (MERGE_X, row chunks +
-// 1, count).
+// 65,536 patterns.  Every block writes its totals to a row of its own, which
+// k_bwd_table sums in a fixed order.  (Added to 64 rows with float atomics,
+// the same totals had made each gradient depend on the order of the atomics,
+// in an ill-conditioned matrix by 1e-3 of it.)  (Summing the rows into G
+// first, then a table kernel over G, took one launch more.  Summed by
+// k_bwd_table's blocks, it took one launch less, but their patterns' row sums
+// then wait for one another: 4096x4096 matrix, 40 instead of 18 + 8 us.)
+// Grid (MERGE_X, row chunks + 1, count).
 constexpr int MERGE_X = 2 * W4 / MERGE_THREADS;
 // Rows per chunk here: a pattern's terms are evaluated once per chunk, so
 // larger chunks than the histogram merge's (one for a decoder layer's
@@ -1815,11 +1949,13 @@ __global__ void __launch_bounds__(MERGE_THREADS) k_grad_top(BatchArgs b) {
     asm volatile("" ::"s"(fmt), "s"(wg_count), "s"(s2), "s"(gy), "s"(M.wsb), "s"(M.max_iter));
     const bool gblock = blockIdx.y == gy - 1;
     const Ws ws = carve_workspace(M.wsb, M.max_iter);
+    float* const row = ws.tx + ((size_t)blockIdx.y * MERGE_X + blockIdx.x) * (2 * K);
     const DevState* st = ws.st;
     const int kmode = st->kmode, w4 = st->w4, lo4 = st->lo4, w8 = st->w8, lo8 = st->lo8;
     float c0[K], c1[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) { c0[j] = ws.cfin[j]; c1[j] = ws.cfin[KMAX + j]; }
+    const auto zero_row = [&]() { if (threadIdx.x < 2 * K) row[threadIdx.x] = 0.f; };
     float gv[GPER];
     uint32_t key[GPER];
 #pragma unroll
@@ -1837,7 +1973,8 @@ __global__ void __launch_bounds__(MERGE_THREADS) k_grad_top(BatchArgs b) {
         const int w = wide ? w8 : w4, lo = wide ? lo8 : lo4;
         const int r0 = blockIdx.y * GT_ROWS;
         const int r1 = min(wg_count, r0 + GT_ROWS);
-        if (r0 >= r1 || (int)(blockIdx.x * MERGE_THREADS) >= 2 * w) return;   // the same for the block
+        if ((int)(blockIdx.x * MERGE_THREADS) >= 2 * w) return;   // the same for the block; its row is not read
+        if (r0 >= r1) { zero_row(); return; }
         const int i = blockIdx.x * MERGE_THREADS + threadIdx.x;
         if (i < 2 * w) {
             const float* part = reinterpret_cast<const float*>(ws.part) + i;
@@ -1857,7 +1994,7 @@ __global__ void __launch_bounds__(MERGE_THREADS) k_grad_top(BatchArgs b) {
     int nz = 0;
 #pragma unroll
     for (int q = 0; q < GPER; ++q) nz |= gv[q] != 0.f;
-    if (!__syncthreads_or(nz)) return;   // nothing to add in this block
+    if (!__syncthreads_or(nz)) { zero_row(); return; }   // nothing to add in this block
     float acc[2 * K];
 #pragma unroll
     for (int j = 0; j < 2 * K; ++j) acc[j] = 0.f;
@@ -1872,123 +2009,158 @@ __global__ void __launch_bounds__(MERGE_THREADS) k_grad_top(BatchArgs b) {
         for (int j = 0; j < K; ++j) {
             const float ga = gv[q] * a[j];
             acc[j] += ga;
-            acc[K + j] = fmaf(ga * d[j], sgnf(v - c0[j]), acc[K + j]);
+            acc[K + j] += mul_sgn(ga * d[j], v - c0[j]);
         }
     }
     EDKM_STAMP_MARK(b, 3);   // patterns done
     const float tot = block_total<2 * K>(acc, red);
     EDKM_STAMP_MARK(b, 4);   // block summed
-    if (threadIdx.x < 2 * K && tot != 0.f) {
-        const int row = (blockIdx.x + 7 * blockIdx.y) % T_WG;   // spread over the rows
-        atomicAdd(&ws.bpart[(size_t)row * PSTRIDE + threadIdx.x], tot);
-    }
+    if (threadIdx.x < 2 * K) row[threadIdx.x] = tot;
 }
 
-// Iteration t = T..1 of the backward: gamma = dL/dC^(t), then per occupied
-// pattern
+// The backward's table phase (rows exchanged as in the forward's).  Iterations
+// t = T..1: gamma = dL/dC^(t), then per occupied pattern
 //   alpha_j = gamma_j (v_u - C^(t)_j) / S^(t)_j,  abar = sum_j a_uj alpha_j,
 //   delta_j = a_uj (alpha_j - abar),
 //   R_u    += sum_j a_uj gamma_j / S^(t)_j - (1/tau) sum_j delta_j sgn(v_u - C^(t-1)_j),
-// and partials of sum_u n_u delta_j sgn(v_u - C^(t-1)_j), which (times 1/tau)
-// make dL/dC^(t-1).  Grid (T_WG, count).
-template <int K>
-__global__ void __launch_bounds__(T_THREADS) k_bwd_iter(BatchArgs b) {
-    EDKM_STAMP_ENTRY(b);
+// and rows of sum_u n_u delta_j sgn(v_u - C^(t-1)_j), which (times 1/tau) make
+// dL/dC^(t-1); those of t = 1 go to bpart, from which
+// k_gather_grad forms dL/dC^(0).  Writes R beside H.  Grid as k_fwd_table's.
+template <int K, int VB>
+__global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, true> / 256)) k_bwd_table(BatchArgs b, int chunks) {
     __shared__ float red[BLOCK_TOTAL_LDS(K)];
+    constexpr int NC = K < 4 ? 4 : K;   // words of a row (unused columns hold 0)
+    __shared__ double cols[8 * K];
     __shared__ float gSsh[K], c1sh[K], c0sh[K];
+    __shared__ int miss;
     const MatArgs& M = b.m[blockIdx.y];
-    const int t = b.t;
-    // the arguments, in one wait (read where they are used, each had cost a
-    // round trip of its own), then the executed iteration count with the loads
+    // the arguments, in one wait
     const int max_iter = M.max_iter, fmt = M.fmt;
     const float s2 = b.s2, inv_tau = b.inv_tau;
-    asm volatile("" ::"s"(max_iter), "s"(fmt), "s"(t), "s"(s2), "s"(inv_tau), "s"(M.wsb));
+    asm volatile("" ::"s"(max_iter), "s"(fmt), "s"(s2), "s"(inv_tau), "s"(M.wsb));
     const Ws ws = carve_workspace(M.wsb, M.max_iter);
-    const DevState* st = ws.st;
-    const int T = st->teff;
-    // Every load first, none waiting for T: the per-pattern inputs, the
-    // partial blocks (columns [0, 2K) of block 0 -- k_grad_top's, used at
-    // t = T and t = T - 1 -- and [0, K) of block t + 1), and the k-vectors of
-    // iterations t - 1, t, t + 1.
-    uint32_t n4[T_KPT];
-    float R4[T_KPT], H4[T_KPT];
-#pragma unroll
-    for (int r = 0; r < T_KPT; ++r) {
-        const int u = table_key(r);
-        n4[r] = ws.counts[u];
-        R4[r] = t < max_iter ? ws.R[u] : 0.f;
-        H4[r] = t == 1 ? ws.H[u] : 0.f;
-    }
-    PartCols<4 * K> pc;
-    const float* b0 = ws.bpart;
-    const float* bn = t < max_iter ? ws.bpart + (size_t)(t + 1) * T_WG * PSTRIDE : nullptr;
-    pc.load([&](int c) -> const float* {
-        return c < 2 * K ? b0 + c : (c < 3 * K && bn ? bn + (c - 2 * K) : nullptr);
-    });
-    float hc1 = 0.f, hc0 = 0.f, hS = 0.f, hS1 = 0.f, hg1 = 0.f;
-    if (threadIdx.x < K) {
-        const int j = threadIdx.x;
-        hc1 = ws.chist[t * KMAX + j];
-        hc0 = ws.chist[(t - 1) * KMAX + j];
-        hS = ws.shist[t * KMAX + j];
-        if (t < max_iter) { hS1 = ws.shist[(t + 1) * KMAX + j]; hg1 = ws.ghist[(t + 1) * KMAX + j]; }
-    }
-    EDKM_STAMP_MARK(b, 2);   // loads issued
-    pc.stage(red);
-    if (t > T) return;
+    const int T = ws.st->teff;
     const bool lead = blockIdx.x == 0;
+    auto vq = [&](int v) { return (int)blockIdx.x + v * (T_WG / VB); };   // virtual block v of this block
+    uint32_t nv[VB][T_KPT];   // counts and R, in registers for the whole launch
+    float Rv[VB][T_KPT];
+    auto counts = [&](int q, uint32_t (&n)[T_KPT], float (&R)[T_KPT]) {
+#pragma unroll
+        for (int r = 0; r < T_KPT; ++r) { n[r] = ws.counts[table_key(q, r)]; R[r] = 0.f; }
+    };
+#pragma unroll
+    for (int v = 0; v < VB; ++v) counts(vq(v), nv[v], Rv[v]);
+    // k_grad_top's rows: `chunks` times those of the window's blocks, then those
+    // of the global G.  Virtual block q sums rows q, q + T_WG, ...; a round of
+    // exchange makes them gamma^(T) and E.  (Each block summing all rows took 4
+    // us longer at k = 8, 8 at k = 16.)
+    const Rows<2 * K> rt{ws.bx + (size_t)max_iter * T_WG * NC};
+    const int nx = (2 * (ws.st->kmode == KEYED_U64 ? ws.st->w8 : ws.st->w4) + MERGE_THREADS - 1) / MERGE_THREADS;
+    auto top_row = [&](int q) {
+        constexpr int U = 16;
+        static_assert(U * T_WG >= TOP_ROWS, "every row is summed");
+        float x[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int k = q + i * T_WG, y = min(k / max(nx, 1), chunks);
+            x[i] = k < chunks * nx + MERGE_X && threadIdx.x < 2 * K
+                       ? ws.tx[((size_t)y * MERGE_X + (k - y * nx)) * (2 * K) + threadIdx.x] : 0.f;
+        }
+        rt.put(q, tree_sum<U>(x));
+    };
+#pragma unroll
+    for (int v = 0; v < VB; ++v) top_row(vq(v));
+    // thread j < K: C^(t), C^(t-1), S^(t) of the iteration (the next one's are
+    // loaded while this one runs), gamma and S of the one before, E
+    const int jk = threadIdx.x % K;
+    float hc1 = 0.f, hc0 = 0.f, hS = 0.f, gm = 0.f, hS1 = 0.f;
     if (threadIdx.x < K) {
-        const int j = threadIdx.x;
-        float gm;
-        if (t == T) {
-            gm = PartCols<4 * K>::total(red, j);
-        } else {
-            gm = PartCols<4 * K>::total(red, 2 * K + j) * inv_tau;
-            if (t + 1 == T) gm += PartCols<4 * K>::total(red, K + j) * inv_tau;
-            if (!(hS1 > 0.f)) gm += hg1;
-        }
-        c1sh[j] = hc1;
-        c0sh[j] = hc0;
-        gSsh[j] = hS > 0.f ? gm / hS : 0.f;
-        if (lead) ws.ghist[t * KMAX + j] = gm;
+        hc1 = ws.chist[T * KMAX + jk];
+        hc0 = ws.chist[(T - 1) * KMAX + jk];
+        hS = ws.shist[T * KMAX + jk];
     }
+    if (threadIdx.x == 0) miss = 0;
+    int round = 0;
     __syncthreads();
-    EDKM_STAMP_MARK(b, 3);   // partial blocks summed, gamma formed
-    float c1[K], c0[K], gS[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) { c1[j] = c1sh[j]; c0[j] = c0sh[j]; gS[j] = gSsh[j]; }
-    float acc[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) acc[j] = 0.f;
-#pragma unroll
-    for (int r = 0; r < T_KPT; ++r) {
-        const int u = table_key(r);
-        const uint32_t n = n4[r];
-        if (n == 0u) continue;
-        if (!key_finite(u, fmt)) {
-            if (t == 1) ws.HR[u] = make_float2(__builtin_nanf(""), __builtin_nanf(""));
-            continue;
+    rt.gather(cols, &miss, round, top_row);
+    const float g_top = (float)Cols<2 * K>::total(cols, jk), e_top = (float)Cols<2 * K>::total(cols, K + jk);
+    if (lead && threadIdx.x < K) ws.ehist[jk] = e_top;   // for dL/dC^(0) where T = 1
+    for (int t = T; t >= 1; --t) {
+        EDKM_STAMP_BEGIN(b, b.t - t);
+        if (threadIdx.x < K) {
+            if (t == T) {
+                gm = g_top;
+            } else {
+                float x = (float)Cols<NC>::total(cols, jk) * inv_tau;
+                if (t + 1 == T) x += e_top * inv_tau;
+                if (!(hS1 > 0.f)) x += gm;
+                gm = x;
+            }
+            c1sh[jk] = hc1;
+            c0sh[jk] = hc0;
+            gSsh[jk] = hS > 0.f ? gm / hS : 0.f;
+            if (lead) ws.ghist[t * KMAX + jk] = gm;
+            hS1 = hS;
+            hc1 = hc0;
+            if (t > 1) {
+                hc0 = ws.chist[(t - 2) * KMAX + jk];
+                hS = ws.shist[(t - 1) * KMAX + jk];
+            }
         }
-        const float v = key_value(u, fmt);
-        float a[K], dev[K], cm;
-        attn_row_sel<K>(v, c0, s2, a, c1, cm);
-        const float direct = softmax_dev<K>(v, a, gS, c1, cm, dev);
-        const float nf = (float)n;
-        float r_ = 0.f;
+        __syncthreads();
+        float c1[K], c0[K], gS[K];
 #pragma unroll
-        for (int j = 0; j < K; ++j) {
-            const float dl = a[j] * dev[j] * sgnf(v - c0[j]);
-            r_ += dl;
-            acc[j] = fmaf(nf, dl, acc[j]);
+        for (int j = 0; j < K; ++j) { c1[j] = uniform(c1sh[j]); c0[j] = uniform(c0sh[j]); gS[j] = uniform(gSsh[j]); }
+        // row q's totals, in threads [0, K); adds this iteration's part to R
+        auto partial = [&](int q, const uint32_t (&n)[T_KPT], float (&R)[T_KPT]) {
+            float acc[K];
+#pragma unroll
+            for (int j = 0; j < K; ++j) acc[j] = 0.f;
+#pragma unroll
+            for (int r = 0; r < T_KPT; ++r) {
+                const uint32_t u = table_key(q, r);
+                if (n[r] == 0u || !key_finite(u, fmt)) continue;
+                const float v = key_value(u, fmt);
+                float a[K], dev[K], cm, gSm;
+                attn_row_sel<K>(v, c0, s2, a, c1, cm, gS, gSm);
+                const float direct = softmax_dev<K>(v, a, gS, c1, cm, gSm, dev);
+                const float nf = (float)n[r];
+                float r_ = 0.f;
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    const float dl = mul_sgn(a[j] * dev[j], v - c0[j]);
+                    r_ += dl;
+                    acc[j] = fmaf(nf, dl, acc[j]);
+                }
+                R[r] = fmaf(-r_, inv_tau, direct) + R[r];
+            }
+            return block_total<K>(acc, red);
+        };
+        const Rows<NC> rows{ws.bx + (size_t)(t - 1) * T_WG * NC};
+#pragma unroll
+        for (int v = 0; v < VB; ++v) {
+            const int q = vq(v);
+            const float tot = partial(q, nv[v], Rv[v]);
+            if (t > 1) {
+                rows.put(q, tot);
+                continue;
+            }
+            if (threadIdx.x < K) ws.bpart[(size_t)q * PSTRIDE + threadIdx.x] = tot;
+#pragma unroll
+            for (int r = 0; r < T_KPT; ++r) {
+                const uint32_t u = table_key(q, r);
+                if (nv[v][r] != 0u) ws.HR[u].y = key_finite(u, fmt) ? Rv[v][r] : __builtin_nanf("");
+            }
         }
-        const float Ru = fmaf(-r_, inv_tau, direct) + (t != T ? R4[r] : 0.f);
-        if (t == 1) ws.HR[u] = make_float2(H4[r], Ru);
-        else ws.R[u] = Ru;
+        EDKM_STAMP_END(b, b.t - t);
+        if (t > 1)
+            rows.gather(cols, &miss, round, [&](int q) {
+                uint32_t n[T_KPT];
+                float R[T_KPT];        // of another block's patterns: that block's to keep
+                counts(q, n, R);
+                rows.put(q, partial(q, n, R));
+            });
     }
-    EDKM_STAMP_MARK(b, 4);   // patterns done
-    const float tot = block_total<K>(acc, red);
-    EDKM_STAMP_MARK(b, 5);   // block summed
-    if (threadIdx.x < K) ws.bpart[((size_t)t * T_WG + blockIdx.x) * PSTRIDE + threadIdx.x] = tot;
 }
 
 // ----------------------------------------------------------------------------
@@ -2045,7 +2217,7 @@ __global__ void __launch_bounds__(D_THREADS) k_dense_iter(BatchArgs b) {
         const float v = key_value(key, M.fmt);
         float a[K];
         float unused;
-        const float r = attn_row_dense_un<K>(v, c, b.s2, a, c, unused);   // normalised below
+        const float r = attn_row_dense_un<K>(v, c, b.s2, a, c, unused, c, unused);   // normalised below
         const float rv = r * v;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
@@ -2169,7 +2341,7 @@ __global__ void __launch_bounds__(D_THREADS) k_dense_btop(BatchArgs b) {
         float h = 0.f;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            const float q = a[j] * d[j] * sgnf(v - c0[j]);
+            const float q = mul_sgn(a[j] * d[j], v - c0[j]);
             h += q;
             acc[j] = fmaf(g, a[j], acc[j]);
             acc[K + j] = fmaf(g, q, acc[K + j]);
@@ -2212,13 +2384,13 @@ __global__ void __launch_bounds__(D_THREADS) k_dense_biter(BatchArgs b) {
         const uint32_t key = M.keys[i];
         if (!key_finite(key, M.fmt)) continue;
         const float v = key_value(key, M.fmt);
-        float a[K], dev[K], cm;
-        attn_row_dense<K>(v, c0, b.s2, a, c1, cm);
-        const float direct = softmax_dev<K>(v, a, gS, c1, cm, dev);
+        float a[K], dev[K], cm, gSm;
+        attn_row_dense<K>(v, c0, b.s2, a, c1, cm, gS, gSm);
+        const float direct = softmax_dev<K>(v, a, gS, c1, cm, gSm, dev);
         float r = 0.f;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            const float dl = a[j] * dev[j] * sgnf(v - c0[j]);
+            const float dl = mul_sgn(a[j] * dev[j], v - c0[j]);
             r += dl;
             acc[j] += dl;
         }
@@ -2317,15 +2489,29 @@ static uint32_t merge_chunks(const BatchArgs& b, int per = MERGE_ROWS) {
     return (rows + per - 1) / per;
 }
 
+// A table phase over the launch's matrices: as few virtual blocks a block as let
+// all blocks run at a time (14 matrices at k = 8, forward and backward: 57 us
+// with one, 66 us with two).
+#define EDKM_TABLE(name, kern, bwd, ...)                                                         \
+    do {                                                                                         \
+        const dim3 tb_(T_THREADS);                                                               \
+        const int need_ = b.count * T_WG;                                                        \
+        static_assert(MAXB * T_WG <= TABLE_BLOCKS<K, 4, bwd> * 4, "a full group fits");          \
+        if (need_ <= TABLE_BLOCKS<K, 1, bwd>)                                                    \
+            EDKM_LAUNCH(name, (kern<K, 1>), dim3(T_WG, b.count), tb_, __VA_ARGS__);              \
+        else if (need_ <= TABLE_BLOCKS<K, 2, bwd> * 2)                                           \
+            EDKM_LAUNCH(name, (kern<K, 2>), dim3(T_WG / 2, b.count), tb_, __VA_ARGS__);          \
+        else if constexpr (MAXB * T_WG > TABLE_BLOCKS<K, 2, bwd> * 2)                            \
+            EDKM_LAUNCH(name, (kern<K, 4>), dim3(T_WG / 4, b.count), tb_, __VA_ARGS__);          \
+    } while (0)
+
 template <int K>
 static hipError_t forward_k(BatchArgs& b, uint32_t grid_np, int max_t, hipStream_t s, const char** where,
                             const PassEvents* ev) {
-    const dim3 tg(T_WG, b.count);
-    for (int t = 1; t <= max_t; ++t) {
-        b.t = t;
-        EDKM_LAUNCH("k_fwd_iter", k_fwd_iter<K>, tg, dim3(T_THREADS), b);
-    }
-    EDKM_LAUNCH("k_fwd_out", k_fwd_out<K>, tg, dim3(T_THREADS), b);
+    b.t = max_t;
+    EDKM_TABLE("k_fwd_iter", k_fwd_table, false, b);
+    EDKM_STAMP_MORE("k_fwd_iter", max_t - 1);
+    EDKM_STAMP_MORE("k_fwd_out", 1);
     EDKM_NPASS(PASS_GATHER_WT, "k_gather_wt", k_gather_wt, dim3(grid_np), dim3(NP_THREADS), b);
     return hipSuccess;
 }
@@ -2333,15 +2519,15 @@ static hipError_t forward_k(BatchArgs& b, uint32_t grid_np, int max_t, hipStream
 template <int K>
 static hipError_t backward_k(BatchArgs& b, uint32_t grid_np, int max_t, hipStream_t s, const char** where,
                              const PassEvents* ev) {
-    const dim3 tg(T_WG, b.count);
     if (b.g_half) EDKM_NPASS(PASS_KEYED_GRAD, "k_keyed_grad", k_keyed_grad<true>, dim3(grid_np), dim3(NP_THREADS), b);
     else EDKM_NPASS(PASS_KEYED_GRAD, "k_keyed_grad", k_keyed_grad<false>, dim3(grid_np), dim3(NP_THREADS), b);
-    EDKM_LAUNCH("k_grad_top", k_grad_top<K>, dim3(MERGE_X, merge_chunks(b, GT_ROWS) + 1, b.count),
+    const int chunks = (int)merge_chunks(b, GT_ROWS);
+    static_assert(MERGE_X * (NP_MAX_WG / GT_ROWS + 1) <= TOP_ROWS, "k_grad_top's rows fit the workspace");
+    EDKM_LAUNCH("k_grad_top", k_grad_top<K>, dim3(MERGE_X, chunks + 1, b.count),
                 dim3(MERGE_THREADS), b);
-    for (int t = max_t; t >= 1; --t) {
-        b.t = t;
-        EDKM_LAUNCH("k_bwd_iter", k_bwd_iter<K>, tg, dim3(T_THREADS), b);
-    }
+    b.t = max_t;
+    EDKM_TABLE("k_bwd_iter", k_bwd_table, true, b, chunks);
+    EDKM_STAMP_MORE("k_bwd_iter", max_t - 1);
     const dim3 gg(grid_np), gb(NP_THREADS);
     if (b.g_half && b.gw_half) EDKM_NPASS(PASS_GATHER_GRAD, "k_gather_grad", (k_gather_grad<true, true>), gg, gb, b);
     else if (b.g_half) EDKM_NPASS(PASS_GATHER_GRAD, "k_gather_grad", (k_gather_grad<true, false>), gg, gb, b);
@@ -2412,9 +2598,10 @@ hipError_t launch_init_unique(BatchArgs& b, uint32_t grid_np, hipStream_t s, con
     return hipSuccess;
 }
 
-hipError_t launch_forward(BatchArgs& b, uint32_t grid_np, int max_t, hipStream_t s, const char** where,
-                          const PassEvents* ev) {
+hipError_t launch_forward(BatchArgs& b, uint32_t grid_np, int max_t, bool empty_rows, hipStream_t s,
+                          const char** where, const PassEvents* ev) {
     (void)hipGetLastError();
+    if (empty_rows) EDKM_LAUNCH("k_empty_rows", k_empty_rows, dim3(T_WG, b.count), dim3(T_THREADS), b);
     set_keep_frac(b);
     EDKM_DISPATCH_K(b.m[0].k, forward_k, b, grid_np, max_t, s, where, ev);
 }
