@@ -127,6 +127,15 @@ edkm_status check_batch(int count, edkm_plan* const* plans, const uint16_t* cons
     return EDKM_OK;
 }
 
+// Blocks of the dense path: one per 4,096 weights up to D_WG, each a chunk of a
+// multiple of 8 weights; no chunk is empty.
+uint32_t dense_split(MatArgs& M) {
+    uint64_t nwg = std::min<uint64_t>((M.n + 4095) / 4096, D_WG);
+    M.chunk = ((M.n + nwg - 1) / nwg + 7) & ~7ull;
+    nwg = (M.n + M.chunk - 1) / M.chunk;
+    return (uint32_t)nwg;
+}
+
 bool tau_ok(float tau) { return std::isfinite(tau) && tau > 0.f && std::isfinite(1.0f / tau); }
 bool eps_ok(float eps) { return std::isfinite(eps) && eps >= 0.f; }
 
@@ -422,15 +431,14 @@ edkm_status edkm_forward_dense(edkm_plan* plan, const uint16_t* w_bits, float ta
     M.wt = w_tilde;
     M.iters_out = iters_out;
     M.attn = attn_out;
-    uint64_t nwg = (P->n + 4095) / 4096;
-    if (nwg > (uint64_t)D_WG) nwg = D_WG;
-    M.chunk = (P->n + nwg - 1) / nwg;
+    M.vec = aligned16(w_bits) && aligned16(w_tilde);
+    const uint32_t nwg = dense_split(M);
     // the dense kernels reuse the workspace's iteration history: whatever
     // state it held is gone once they launch, whether or not they succeed
     P->stage = PLANNED;
     P->keys = nullptr;
     const char* where = "";
-    const hipError_t e = launch_forward_dense(b, (uint32_t)nwg, stream, &where, &P->ev);
+    const hipError_t e = launch_forward_dense(b, nwg, stream, &where, &P->ev);
     if (e != hipSuccess) return hip_fail(&plan, 0, 1, e, where);
     P->stage = DENSE_FORWARD;
     P->keys = w_bits;
@@ -454,11 +462,10 @@ edkm_status edkm_backward_dense(edkm_plan* plan, const uint16_t* w_bits, const f
     M.g = grad_w_tilde;
     M.gw = grad_w;
     M.gc = grad_c;
-    uint64_t nwg = (P->n + 4095) / 4096;
-    if (nwg > (uint64_t)D_WG) nwg = D_WG;
-    M.chunk = (P->n + nwg - 1) / nwg;
+    M.vec = aligned16(w_bits) && aligned16(grad_w_tilde) && aligned16(grad_w);
+    const uint32_t nwg = dense_split(M);
     const char* where = "";
-    const hipError_t e = launch_backward_dense(b, (uint32_t)nwg, stream, &where, &P->ev);
+    const hipError_t e = launch_backward_dense(b, nwg, stream, &where, &P->ev);
     if (e != hipSuccess) return hip_fail(&plan, 0, 1, e, where);
     return EDKM_OK;
 }

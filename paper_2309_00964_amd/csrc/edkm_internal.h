@@ -27,8 +27,8 @@ constexpr int TOP_ROWS = 760;         // rows of the backward's first sums, at m
 constexpr int KMAX = 16;
 constexpr int PSTRIDE = 32;           // floats per table-phase partial row (2 * KMAX)
 constexpr int MAXB = EDKM_LAUNCH_GROUP;   // matrices per launch
-constexpr int D_WG = 1024;            // dense path: max workgroups
-constexpr int D_THREADS = 256;
+constexpr int D_WG = 256;             // dense path: max workgroups
+constexpr int D_THREADS = 1024;
 
 // Device-side per-matrix state (in the workspace).
 struct DevState {
@@ -58,7 +58,7 @@ struct Ws {
     uint32_t* bx;       // [(max_iter + 2) * T_WG * KMAX]  the same of the backward: its iterations', its first sums'
     float* tx;          // [TOP_ROWS * 2 * KMAX]  backward: first sums (k_grad_top's rows)
     float* bpart;       // [T_WG * PSTRIDE]  backward: the partials of t = 1
-    float* dpart;       // [D_WG * PSTRIDE]  dense-path partials
+    float* dpart;       // [3 * D_WG * PSTRIDE]  dense-path partials: two in turn for the iterations, the first sums'
     int2* span;         // [NP_MAX_WG]  histogram partial spans
     float* cfin;        // [2 * KMAX]  C^(T-1), C^(T) of the last forward (at a fixed place)
     uint32_t* part;     // [NP_MAX_WG * ROW4]  N-pass partial rows
@@ -153,7 +153,7 @@ __host__ __device__ inline Layout layout(int max_iter) {
     L.bx = take(row + (size_t)2 * T_WG * KMAX * sizeof(uint32_t));
     L.tx = take((size_t)TOP_ROWS * 2 * KMAX * sizeof(float));
     L.bpart = take((size_t)T_WG * PSTRIDE * sizeof(float));
-    L.dpart = take((size_t)D_WG * PSTRIDE * sizeof(float));
+    L.dpart = take((size_t)3 * D_WG * PSTRIDE * sizeof(float));
     L.span = take(NP_MAX_WG * sizeof(int2));
     L.part = take((size_t)NP_MAX_WG * ROW4 * sizeof(uint32_t));
     L.pidx = take(NKEYS);

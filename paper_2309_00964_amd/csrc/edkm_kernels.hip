@@ -134,10 +134,17 @@ __device__ __forceinline__ uint32_t to_half_bits(float x, int fmt) {
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-// y sgn(x), sgn(0) = 0
-__device__ __forceinline__ float mul_sgn(float y, float x) {
-    const float z = __uint_as_float(__float_as_uint(y) ^ (__float_as_uint(x) & 0x80000000u));
-    return x == 0.f ? 0.f : z;
+// y sgn(x) for x != 0, and for all x with sgn(0) = 0
+__device__ __forceinline__ float flip_sign(float y, float x) {
+    return __uint_as_float(__float_as_uint(y) ^ (__float_as_uint(x) & 0x80000000u));
+}
+__device__ __forceinline__ float mul_sgn(float y, float x) { return x == 0.f ? 0.f : flip_sign(y, x); }
+
+// 1 / x for normal x: the hardware's estimate and one Newton step, within an ulp
+// of the quotient at a third of the division's instructions.
+__device__ __forceinline__ float recip(float x) {
+    const float r = __builtin_amdgcn_rcpf(x);
+    return fmaf(fmaf(-x, r, 1.0f), r, r);
 }
 
 // One attention row: a_j = softmax_j(-|v - c_j| / tau), with s2 = log2(e) / tau,
@@ -172,7 +179,7 @@ __device__ __forceinline__ float attn_row_sel_un(float v, const float (&c)[K], f
         a[j] = __builtin_amdgcn_exp2f(-d * s2);
         sum += a[j];
     }
-    return 1.0f / sum;
+    return recip(sum);
 }
 
 template <int K>
@@ -199,21 +206,43 @@ __device__ __forceinline__ void attn_row_sel(float v, const float (&c)[K], float
 // as in attn_row_sel (nearest centroid, first on ties).
 constexpr float DENSE_FAST_X = 256.f;
 
+// The row alone, unnormalised, with the factor it returns.
+template <int K>
+__device__ __forceinline__ float attn_row_dense_near(float v, const float (&c)[K], float s2, float (&a)[K]) {
+    float d[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) d[j] = v - c[j];
+    float xm = fabsf(d[0]);
+#pragma unroll
+    for (int j = 1; j < K; ++j) xm = fminf(xm, fabsf(d[j]));   // two to an instruction (v_min3)
+    const float off = xm * s2;
+    if (off <= DENSE_FAST_X) {
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            a[j] = __builtin_amdgcn_exp2f(fmaf(-fabsf(d[j]), s2, off));
+            sum += a[j];
+        }
+        return recip(sum);
+    }
+    float unused;
+    attn_row_sel<K>(v, c, s2, a, c, unused);
+    return 1.0f;
+}
+
 // Unnormalised form: a_j up to the factor r it returns (r = 1 after the
-// careful row, which normalises itself).
+// careful row, which normalises itself).  xm: the nearest centroid's distance.
 template <int K>
 __device__ __forceinline__ float attn_row_dense_un(float v, const float (&c)[K], float s2, float (&a)[K],
-                                                   const float (&e)[K], float& em, const float (&f)[K],
-                                                   float& fm) {
+                                                   const float (&e)[K], float& em, float& xm) {
     float d[K];
     d[0] = fabsf(v - c[0]);
-    float xm = d[0];
+    xm = d[0];
     em = e[0];
-    fm = f[0];
 #pragma unroll
     for (int j = 1; j < K; ++j) {
         d[j] = fabsf(v - c[j]);
-        if (d[j] < xm) { xm = d[j]; em = e[j]; fm = f[j]; }
+        if (d[j] < xm) { xm = d[j]; em = e[j]; }
     }
     const float off = xm * s2;
     if (off <= DENSE_FAST_X) {
@@ -223,24 +252,18 @@ __device__ __forceinline__ float attn_row_dense_un(float v, const float (&c)[K],
             a[j] = __builtin_amdgcn_exp2f(fmaf(-d[j], s2, off));
             sum += a[j];
         }
-        return 1.0f / sum;
+        return recip(sum);
     }
-    attn_row_sel<K>(v, c, s2, a, e, em, f, fm);
+    attn_row_sel<K>(v, c, s2, a, e, em);
     return 1.0f;
 }
 
 template <int K>
 __device__ __forceinline__ void attn_row_dense(float v, const float (&c)[K], float s2, float (&a)[K],
-                                               const float (&e)[K], float& em, const float (&f)[K], float& fm) {
-    const float r = attn_row_dense_un<K>(v, c, s2, a, e, em, f, fm);
+                                               const float (&e)[K], float& em, float& xm) {
+    const float r = attn_row_dense_un<K>(v, c, s2, a, e, em, xm);
 #pragma unroll
     for (int j = 0; j < K; ++j) a[j] *= r;
-}
-template <int K>
-__device__ __forceinline__ void attn_row_dense(float v, const float (&c)[K], float s2, float (&a)[K],
-                                               const float (&e)[K], float& em) {
-    float unused;
-    attn_row_dense<K>(v, c, s2, a, e, em, c, unused);
 }
 
 // Deviations d_j = C^(T)_j - W~ of one map row a, W~ = sum_j a_j C^(T)_j,
@@ -265,7 +288,8 @@ __device__ __forceinline__ float centroid_dev(const float (&a)[K], const float (
 //   dev_j = alpha_j - sum_i a_i alpha_i,  alpha_j = gS_j (v - c1_j),
 // written around the reference cm = c1_m, gm = gS_m (m the nearest centroid) as
 //   dev_j = (gS_j - gm - db)(v - cm) - (gS_j (c1_j - cm) - hb),
-//   db = sum_i a_i (gS_i - gm),  hb = sum_i a_i gS_i (c1_i - cm),
+//   db = sum_i a_i (gS_i - gm),  hb = sum_i a_i gS_i (c1_i - cm)
+// (any gm gives the same; the dense path passes 0),
 // which subtracts neither two terms of size |v| nor, for a nearly one-hot row,
 // two nearly equal gS (their rounding error, times |v| / tau, was dL/dw's
 // largest for weights far from zero).  Returns sum_i a_i gS_i = gm + db.
@@ -282,6 +306,11 @@ __device__ __forceinline__ float softmax_dev(float v, const float (&a)[K], const
 #pragma unroll
     for (int j = 0; j < K; ++j) dev[j] = fmaf((gS[j] - gm) - db, w1, -fmaf(gS[j], c1[j] - cm, -hb));
     return gm + db;
+}
+
+// A value that is the same in every lane, moved to a scalar register.
+__device__ __forceinline__ float uniform(float x) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
 
 // DPP lane moves: a VALU operand read from another lane of the same row of 16
@@ -1117,11 +1146,6 @@ constexpr long long XW_WAIT = EDKM_XW_WAIT;  // wall-clock ticks (100 MHz): 20 u
 // waits for one that has not started.
 template <int K, int NVB, bool BWD>
 constexpr int TABLE_BLOCKS = K == 16 && BWD ? (NVB == 1 ? 768 : 512) : 1024;
-
-// A value that is the same in every lane, moved to a scalar register.
-__device__ __forceinline__ float uniform(float x) {
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
-}
 
 __device__ __forceinline__ void xw_put(uint32_t* p, float x) {
     uint32_t v = __float_as_uint(x);
@@ -2159,269 +2183,355 @@ __global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, true> / 256)) 
 // ----------------------------------------------------------------------------
 // dense (non-uniquified) comparison path: one attention row per weight
 
-__device__ __forceinline__ bool dense_range(const MatArgs& M, uint64_t& beg, uint64_t& end) {
-    beg = (uint64_t)blockIdx.x * M.chunk;
-    end = min(M.n, beg + M.chunk);
-    return beg < end;
+// Bound by VALU issue (about 10 instructions a map entry in the iterations, 25
+// in the backward's).  4096x4096 at 3 bits: the whole step 951 -> 706 us with
+// one 1024-thread block a CU that forms the centroids itself from the previous
+// launch's rows (11 single-block launches less), keys and gradients loaded 4 or
+// 8 to a thread, the nearest distance by minima (k_dense_iter 51 -> 40 us), a
+// Newton reciprocal for the division, and d|x|/dx at 0 looked at only where a
+// weight lies on a centroid (k_dense_biter 94 -> 86 us).
+
+// The weights of a block's chunk: fn(i, key, u) for each, in groups of GW
+// consecutive ones per thread (u: place in the group), loaded together where
+// the buffers are 16-byte aligned.  pre(i) is called before a group's fn, and
+// post(i) after it, on whole aligned groups; a single weight has fn(i, key, -1).
+template <int GW, class Pre, class Fn, class Post>
+__device__ __forceinline__ void dense_for(const MatArgs& M, Pre pre, Fn fn, Post post) {
+    static_assert(GW == 4 || GW == 8, "one 8- or 16-byte load of keys");
+    const uint64_t beg = (uint64_t)blockIdx.x * M.chunk, end = min(M.n, beg + M.chunk);   // chunk: a multiple of 8
+    uint64_t one = beg;   // first weight that is done on its own
+    if (M.vec) {
+        for (uint64_t i = beg + (uint64_t)GW * threadIdx.x; i + GW <= end; i += (uint64_t)GW * D_THREADS) {
+            uint32_t w[GW / 2];
+            if constexpr (GW == 8) {
+                const uint4 q = ld_u4(M.keys + i);
+                w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
+            } else {
+                const uint2 q = ld_u2(M.keys + i);
+                w[0] = q.x; w[1] = q.y;
+            }
+            pre(i);
+#pragma unroll
+            for (int u = 0; u < GW; ++u) fn(i + u, u & 1 ? w[u / 2] >> 16 : w[u / 2] & 0xFFFFu, u);
+            post(i);
+        }
+        one = max(beg, end & ~(uint64_t)(GW - 1));
+    }
+    for (uint64_t i = one + threadIdx.x; i < end; i += D_THREADS) fn(i, (uint32_t)M.keys[i], -1);
 }
 
-// Fixed-order sum of the first nrow dense partial rows, columns [c0, c0+ncol),
-// by one block of 1024 threads; result in out[0..ncol) (LDS).
-__device__ __forceinline__ void reduce_dparts(const float* part, int nrow, int c0, int ncol,
-                                              float* scratch /*16*32*/, float* out) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int j = 0; j < ncol; ++j) {
-        float x = threadIdx.x < nrow ? part[threadIdx.x * PSTRIDE + c0 + j] : 0.f;
-        x = wave_sum(x);
-        if (lane == 0) scratch[wave * PSTRIDE + j] = x;
-    }
+// Column totals of the dense path's partial rows (one a block of the previous
+// launch, PSTRIDE floats apart), in a fixed order and in double precision, in
+// out[0..NC) (LDS).  Every block of a launch forms them for itself at its
+// start: a launch of one block in between had taken 7-10 us.
+constexpr int D_WAVES = D_THREADS / 64;
+template <int NC>
+__device__ __forceinline__ void dense_totals(const float* part, int nrow, double* red /*D_WAVES * NC*/, double* out) {
+    const int c = threadIdx.x % NC, lane = threadIdx.x & 63;
+    double y = 0.0;
+    for (int r = threadIdx.x / NC; r < nrow; r += D_THREADS / NC) y += part[r * PSTRIDE + c];
+    y = wave_cols<NC>(y);
+    if (lane < NC) red[(threadIdx.x >> 6) * NC + lane] = y;
     __syncthreads();
-    if (threadIdx.x < ncol) {
-        float s = 0.f;
-        for (int w = 0; w < 16; ++w) s += scratch[w * PSTRIDE + threadIdx.x];
-        out[threadIdx.x] = s;
+    if (threadIdx.x < NC) {
+        double x = 0.0;
+#pragma unroll
+        for (int w = 0; w < D_WAVES; ++w) x += red[w * NC + threadIdx.x];
+        out[threadIdx.x] = x;
     }
     __syncthreads();
 }
 
+// This block's partial row: the block's sums of NV values a thread.
+template <int NV>
+__device__ __forceinline__ void dense_row(const float (&v)[NV], float* scratch, float* out, float* row) {
+    block_sum<NV, D_THREADS>(v, scratch, out);
+    if (threadIdx.x < NV) row[(size_t)blockIdx.x * PSTRIDE + threadIdx.x] = out[threadIdx.x];
+}
+__device__ __forceinline__ float* dense_part(const Ws& ws, int i) { return ws.dpart + (size_t)i * D_WG * PSTRIDE; }
+
+// C^(t-1) from the rows of iteration t - 1 (t = 1: c_in), into c1 (LDS), with
+// C^(t-2) in c0; the first block writes the history.  Returns false once the
+// early stop has ended the iteration (T = t - 1 or an earlier one).
+template <int K>
+__device__ __forceinline__ bool dense_centroids(const MatArgs& M, const Ws& ws, int t, float eps, float* c1,
+                                                float* c0, double* red, double* tot, int* stop) {
+    const bool lead = blockIdx.x == 0;
+    DevState* st = ws.st;
+    const bool done = t > 1 && st->conv;
+    if (threadIdx.x == 0) *stop = 0;
+    if (t > 1 && !done) dense_totals<2 * K>(dense_part(ws, (t - 1) & 1), (int)gridDim.x, red, tot);
+    else __syncthreads();
+    if (done) return false;
+    if (threadIdx.x < K) {
+        const int j = threadIdx.x;
+        if (t == 1) {
+            const float c = M.c_in[j];
+            c1[j] = c;
+            if (lead) { ws.chist[j] = c; ws.shist[j] = 0.f; }
+        } else {
+            const double S = tot[j], P = tot[K + j];
+            const float cprev = ws.chist[(t - 2) * KMAX + j], cn = S > 0.0 ? (float)(P / S) : cprev;
+            c1[j] = cn;
+            c0[j] = cprev;
+            if (lead) { ws.chist[(t - 1) * KMAX + j] = cn; ws.shist[(t - 1) * KMAX + j] = (float)S; }
+            if (!(fabsf(cn - cprev) <= eps)) *stop = 1;
+        }
+    }
+    __syncthreads();
+    return !(t > 1 && eps > 0.f && *stop == 0);
+}
+
+// Iteration t: this block's row of S_j = sum a_ij, P_j = sum a_ij v_i with the
+// map of C^(t-1).
 template <int K>
 __global__ void __launch_bounds__(D_THREADS) k_dense_iter(BatchArgs b) {
     EDKM_STAMP_ENTRY(b);
-    __shared__ float tot[2 * K];
-    __shared__ float scratch[D_THREADS / 64 * 2 * K];
-    __shared__ float csh[K];
-    const MatArgs& M = b.m[0];
-    const Ws ws = carve_workspace(M.wsb, M.max_iter);
-    const int t = b.t;
-    if (t > 1 && ws.st->conv) return;
-    if (threadIdx.x < K) csh[threadIdx.x] = t == 1 ? M.c_in[threadIdx.x] : ws.chist[(t - 1) * KMAX + threadIdx.x];
-    __syncthreads();
-    float c[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) c[j] = csh[j];
-    float acc[2 * K];
-#pragma unroll
-    for (int j = 0; j < 2 * K; ++j) acc[j] = 0.f;
-    uint64_t beg, end;
-    dense_range(M, beg, end);
-    for (uint64_t i = beg + threadIdx.x; i < end; i += D_THREADS) {
-        const uint32_t key = M.keys[i];
-        if (!key_finite(key, M.fmt)) continue;
-        const float v = key_value(key, M.fmt);
-        float a[K];
-        float unused;
-        const float r = attn_row_dense_un<K>(v, c, b.s2, a, c, unused, c, unused);   // normalised below
-        const float rv = r * v;
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-            acc[j] = fmaf(a[j], r, acc[j]);
-            acc[K + j] = fmaf(a[j], rv, acc[K + j]);
-        }
-    }
-    block_sum<2 * K, D_THREADS>(acc, scratch, tot);
-    if (threadIdx.x < 2 * K) ws.dpart[(size_t)blockIdx.x * PSTRIDE + threadIdx.x] = tot[threadIdx.x];
-}
-
-// One block: C^(t) from the dense partials, history, early stop.
-template <int K>
-__global__ void __launch_bounds__(1024) k_dense_fin(BatchArgs b, int nrow) {
-    EDKM_STAMP_ENTRY(b);
-    __shared__ float scratch[16 * PSTRIDE];
-    __shared__ float tot[2 * K];
+    __shared__ double red[D_WAVES * 2 * K], tot[2 * K];
+    __shared__ float scratch[D_WAVES * 2 * K], rsum[2 * K];
+    __shared__ float csh[K], c0sh[K];
     __shared__ int stop;
     const MatArgs& M = b.m[0];
     const Ws ws = carve_workspace(M.wsb, M.max_iter);
-    DevState* st = ws.st;
-    const int t = b.t;
-    if (t > 1 && st->conv) return;
-    reduce_dparts(ws.dpart, nrow, 0, 2 * K, scratch, tot);
-    if (threadIdx.x == 0) stop = 0;
-    __syncthreads();
-    if (threadIdx.x < K) {
-        const int j = threadIdx.x;
-        const float cprev = t == 1 ? M.c_in[j] : ws.chist[(t - 1) * KMAX + j];
-        if (t == 1) { ws.chist[j] = cprev; ws.shist[j] = 0.f; }
-        const float S = tot[j], P = tot[K + j];
-        const float cn = S > 0.f ? P / S : cprev;
-        ws.chist[t * KMAX + j] = cn;
-        ws.shist[t * KMAX + j] = S;
-        if (!(fabsf(cn - cprev) <= b.eps)) atomicOr(&stop, 1);
+    const int t = b.t, fmt = M.fmt;
+    const float s2 = b.s2;
+    if (!dense_centroids<K>(M, ws, t, b.eps, csh, c0sh, red, tot, &stop)) {
+        // max_j |C^(t-1) - C^(t-2)| <= eps now or before
+        if (blockIdx.x == 0 && threadIdx.x == 0 && !ws.st->conv) { ws.st->teff = t - 1; ws.st->conv = 1; }
+        return;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        if (b.eps > 0.f && stop == 0) { st->conv = 1; st->teff = t; }
-        else { st->conv = 0; st->teff = t; }
-    }
-}
-
-template <int K>
-__global__ void __launch_bounds__(D_THREADS) k_dense_out(BatchArgs b) {
-    EDKM_STAMP_ENTRY(b);
-    const MatArgs& M = b.m[0];
-    const Ws ws = carve_workspace(M.wsb, M.max_iter);
-    const int T = ws.st->teff;
-    __shared__ float c1sh[K], c0sh[K];
-    if (threadIdx.x < K) {
-        c1sh[threadIdx.x] = ws.chist[T * KMAX + threadIdx.x];
-        c0sh[threadIdx.x] = ws.chist[(T - 1) * KMAX + threadIdx.x];
-    }
-    __syncthreads();
-    float c1[K], c0[K];
+    if (blockIdx.x == 0 && threadIdx.x == 0 && t == 1) ws.st->conv = 0;
+    float c[K];
 #pragma unroll
-    for (int j = 0; j < K; ++j) { c1[j] = c1sh[j]; c0[j] = c0sh[j]; }
-    if (blockIdx.x == 0) {
-        if (threadIdx.x < K) M.c_out[threadIdx.x] = ws.chist[T * KMAX + threadIdx.x];
-        if (threadIdx.x == 0 && M.iters_out) *M.iters_out = T;
-    }
-    uint64_t beg, end;
-    dense_range(M, beg, end);
-    for (uint64_t i = beg + threadIdx.x; i < end; i += D_THREADS) {
-        const uint32_t key = M.keys[i];
-        float wv;
-        float a[K];
-        if (key_finite(key, M.fmt)) {
-            const float v = key_value(key, M.fmt);
-            float unused;
-            attn_row_dense<K>(v, c0, b.s2, a, c0, unused);
-            wv = 0.f;
-#pragma unroll
-            for (int j = 0; j < K; ++j) wv = fmaf(a[j], c1[j], wv);
-        } else {
-            wv = __builtin_nanf("");
-#pragma unroll
-            for (int j = 0; j < K; ++j) a[j] = __builtin_nanf("");
-        }
-        if (b.out_half) reinterpret_cast<uint16_t*>(M.wt)[i] = (uint16_t)to_half_bits(wv, M.fmt);
-        else reinterpret_cast<float*>(M.wt)[i] = wv;
-        if (M.attn) {
-#pragma unroll
-            for (int j = 0; j < K; ++j) M.attn[i * K + j] = a[j];
-        }
-    }
-}
-
-// Dense backward, direct use of A^(T): dL/dw_i = g_i H_i, and partials of gamma and E.
-template <int K>
-__global__ void __launch_bounds__(D_THREADS) k_dense_btop(BatchArgs b) {
-    EDKM_STAMP_ENTRY(b);
-    __shared__ float tot[2 * K];
-    __shared__ float scratch[D_THREADS / 64 * 2 * K];
-    const MatArgs& M = b.m[0];
-    const Ws ws = carve_workspace(M.wsb, M.max_iter);
-    const int T = ws.st->teff;
-    __shared__ float c1sh[K], c0sh[K];
-    if (threadIdx.x < K) {
-        c1sh[threadIdx.x] = ws.chist[T * KMAX + threadIdx.x];
-        c0sh[threadIdx.x] = ws.chist[(T - 1) * KMAX + threadIdx.x];
-    }
-    __syncthreads();
-    float c1[K], c0[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) { c1[j] = c1sh[j]; c0[j] = c0sh[j]; }
+    for (int j = 0; j < K; ++j) c[j] = uniform(csh[j]);
     float acc[2 * K];
 #pragma unroll
     for (int j = 0; j < 2 * K; ++j) acc[j] = 0.f;
-    uint64_t beg, end;
-    dense_range(M, beg, end);
-    for (uint64_t i = beg + threadIdx.x; i < end; i += D_THREADS) {
-        const uint32_t key = M.keys[i];
-        if (!key_finite(key, M.fmt)) { M.gw[i] = __builtin_nanf(""); continue; }
-        const float v = key_value(key, M.fmt);
-        const float g = M.g[i];
-        float a[K], d[K], c1m;
-        attn_row_dense<K>(v, c0, b.s2, a, c1, c1m);
-        centroid_dev<K>(a, c1, c1m, d);
-        float h = 0.f;
+    dense_for<8>(M, [](uint64_t) {},
+        [&](uint64_t, uint32_t key, int) {
+            if (!key_finite(key, fmt)) return;
+            const float v = key_value(key, fmt);
+            float a[K];
+            const float r = attn_row_dense_near<K>(v, c, s2, a);
+            const float rv = r * v;
 #pragma unroll
-        for (int j = 0; j < K; ++j) {
-            const float q = mul_sgn(a[j] * d[j], v - c0[j]);
-            h += q;
-            acc[j] = fmaf(g, a[j], acc[j]);
-            acc[K + j] = fmaf(g, q, acc[K + j]);
-        }
-        M.gw[i] = -g * h * b.inv_tau;
-    }
-    block_sum<2 * K, D_THREADS>(acc, scratch, tot);
-    if (threadIdx.x < 2 * K) ws.dpart[(size_t)blockIdx.x * PSTRIDE + threadIdx.x] = tot[threadIdx.x];
+            for (int j = 0; j < K; ++j) {
+                acc[j] = fmaf(a[j], r, acc[j]);
+                acc[K + j] = fmaf(a[j], rv, acc[K + j]);
+            }
+        },
+        [](uint64_t) {});
+    dense_row<2 * K>(acc, scratch, rsum, dense_part(ws, t & 1));
 }
 
-// Dense backward iteration t (reads gamma^(t) from ghist).
+// C^(T), T, c_out and W~_i = sum_j a^(T)_ij C^(T)_j (a^(T) from C^(T-1)); the map
+// itself where it is asked for.
+template <int K>
+__global__ void __launch_bounds__(D_THREADS) k_dense_out(BatchArgs b) {
+    EDKM_STAMP_ENTRY(b);
+    __shared__ double red[D_WAVES * 2 * K], tot[2 * K];
+    __shared__ float c1sh[K], c0sh[K];
+    __shared__ int stop;
+    const MatArgs& M = b.m[0];
+    const Ws ws = carve_workspace(M.wsb, M.max_iter);
+    const bool conv = ws.st->conv;   // by an iteration's launch: T is in the state
+    int T = M.max_iter;
+    if (conv) {
+        T = ws.st->teff;
+        if (threadIdx.x < K) {
+            c1sh[threadIdx.x] = ws.chist[T * KMAX + threadIdx.x];
+            c0sh[threadIdx.x] = ws.chist[(T - 1) * KMAX + threadIdx.x];
+        }
+        __syncthreads();
+    } else {
+        dense_centroids<K>(M, ws, T + 1, 0.f, c1sh, c0sh, red, tot, &stop);
+    }
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < K) M.c_out[threadIdx.x] = c1sh[threadIdx.x];
+        if (threadIdx.x == 0) {
+            ws.st->teff = T;
+            if (M.iters_out) *M.iters_out = T;
+        }
+    }
+    const int fmt = M.fmt;
+    const float s2 = b.s2;
+    const bool half = b.out_half, vec = M.vec;
+    float* const attn = M.attn;
+    float* const outf = reinterpret_cast<float*>(M.wt);
+    uint16_t* const outh = reinterpret_cast<uint16_t*>(M.wt);
+    float c1[K], c0[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) { c1[j] = uniform(c1sh[j]); c0[j] = uniform(c0sh[j]); }
+    float o[4];
+    dense_for<4>(M, [](uint64_t) {},
+        [&](uint64_t i, uint32_t key, int u) {
+            float wv;
+            float a[K];
+            if (key_finite(key, fmt)) {
+                const float r = attn_row_dense_near<K>(key_value(key, fmt), c0, s2, a);
+                wv = 0.f;
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    a[j] *= r;
+                    wv = fmaf(a[j], c1[j], wv);
+                }
+            } else {
+                wv = __builtin_nanf("");
+#pragma unroll
+                for (int j = 0; j < K; ++j) a[j] = __builtin_nanf("");
+            }
+            if (attn) {
+#pragma unroll
+                for (int j = 0; j < K; ++j) attn[i * K + j] = a[j];
+            }
+            if (u >= 0) o[u & 3] = wv;
+            else if (half) outh[i] = (uint16_t)to_half_bits(wv, fmt);
+            else outf[i] = wv;
+        },
+        [&](uint64_t i) {
+            if (half) st_u2_nt(outh + i, make_uint2(to_half_bits(o[0], fmt) | (to_half_bits(o[1], fmt) << 16),
+                                                    to_half_bits(o[2], fmt) | (to_half_bits(o[3], fmt) << 16)));
+            else st_f4_nt(outf + i, make_float4(o[0], o[1], o[2], o[3]));
+        });
+}
+
+// Dense backward, direct use of A^(T): dL/dw_i = g_i H_i, and rows of gamma and E.
+template <int K>
+__global__ void __launch_bounds__(D_THREADS) k_dense_btop(BatchArgs b) {
+    EDKM_STAMP_ENTRY(b);
+    __shared__ float scratch[D_WAVES * 2 * K], rsum[2 * K];
+    const MatArgs& M = b.m[0];
+    const Ws ws = carve_workspace(M.wsb, M.max_iter);
+    const int T = ws.st->teff, fmt = M.fmt;
+    const float s2 = b.s2, inv_tau = b.inv_tau;
+    float c1[K], c0[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        c1[j] = uniform(ws.chist[T * KMAX + j]);
+        c0[j] = uniform(ws.chist[(T - 1) * KMAX + j]);
+    }
+    const float* const gp = M.g;
+    float* const gw = M.gw;
+    float acc[2 * K];
+#pragma unroll
+    for (int j = 0; j < 2 * K; ++j) acc[j] = 0.f;
+    float g4[4], o[4];
+    dense_for<4>(M,
+        [&](uint64_t i) { const float4 x = ld_f4_nt(gp + i); g4[0] = x.x; g4[1] = x.y; g4[2] = x.z; g4[3] = x.w; },
+        [&](uint64_t i, uint32_t key, int u) {
+            float out = __builtin_nanf("");
+            if (key_finite(key, fmt)) {
+                const float v = key_value(key, fmt);
+                const float g = u >= 0 ? g4[u & 3] : gp[i];
+                float a[K], d[K], c1m;
+                float xm, h = 0.f;
+                attn_row_dense<K>(v, c0, s2, a, c1, c1m, xm);
+                centroid_dev<K>(a, c1, c1m, d);
+                auto add = [&](auto sgn) {
+#pragma unroll
+                    for (int j = 0; j < K; ++j) {
+                        const float q = sgn(a[j] * d[j], v - c0[j]);
+                        h += q;
+                        acc[j] = fmaf(g, a[j], acc[j]);
+                        acc[K + j] = fmaf(g, q, acc[K + j]);
+                    }
+                };
+                if (xm == 0.f) add([](float y, float x) { return mul_sgn(y, x); });
+                else add([](float y, float x) { return flip_sign(y, x); });
+                out = -g * h * inv_tau;
+            }
+            if (u >= 0) o[u & 3] = out;
+            else gw[i] = out;
+        },
+        [&](uint64_t i) { *reinterpret_cast<float4*>(gw + i) = make_float4(o[0], o[1], o[2], o[3]); });
+    dense_row<2 * K>(acc, scratch, rsum, dense_part(ws, 2));
+}
+
+// dL/dC^(t) (thread j < K) from the rows of the launch before: the first sums'
+// at t = T, iteration t + 1's below.
+template <int K>
+__device__ __forceinline__ float dense_gamma(const Ws& ws, int t, int T, int nrow, float inv_tau, double* red, double* tot) {
+    constexpr int NC = K < 4 ? 4 : K;   // columns past K are not used
+    if (t == T) dense_totals<2 * K>(dense_part(ws, 2), nrow, red, tot);
+    else dense_totals<NC>(dense_part(ws, (t + 1) & 1), nrow, red, tot);
+    if (threadIdx.x >= K) return 0.f;
+    const int j = threadIdx.x;
+    if (t == T) {
+        if (blockIdx.x == 0) ws.ehist[j] = (float)tot[K + j] * inv_tau;
+        return (float)tot[j];
+    }
+    float gm = (float)tot[j] * inv_tau;
+    if (t + 1 == T) gm += ws.ehist[j];
+    if (!(ws.shist[(t + 1) * KMAX + j] > 0.f)) gm += ws.ghist[(t + 1) * KMAX + j];
+    return gm;
+}
+
+// Dense backward iteration t.
 template <int K>
 __global__ void __launch_bounds__(D_THREADS) k_dense_biter(BatchArgs b) {
     EDKM_STAMP_ENTRY(b);
-    __shared__ float tot[K];
-    __shared__ float scratch[D_THREADS / 64 * K];
-    __shared__ float c1sh[K], c0sh[K], gSsh[K];
+    __shared__ double red[D_WAVES * 2 * K], tot[2 * K < 4 ? 4 : 2 * K];
+    __shared__ float scratch[D_WAVES * K], rsum[K];
+    __shared__ float gSsh[K];
     const MatArgs& M = b.m[0];
     const Ws ws = carve_workspace(M.wsb, M.max_iter);
-    const int T = ws.st->teff;
-    const int t = b.t;
+    const int T = ws.st->teff, t = b.t, fmt = M.fmt;
+    const float s2 = b.s2, inv_tau = b.inv_tau;
     if (t > T) return;
+    const float gm = dense_gamma<K>(ws, t, T, (int)gridDim.x, inv_tau, red, tot);
     if (threadIdx.x < K) {
-        const int j = threadIdx.x;
-        c1sh[j] = ws.chist[t * KMAX + j];
-        c0sh[j] = ws.chist[(t - 1) * KMAX + j];
-        const float S = ws.shist[t * KMAX + j];
-        gSsh[j] = S > 0.f ? ws.ghist[t * KMAX + j] / S : 0.f;
+        const float S = ws.shist[t * KMAX + threadIdx.x];
+        gSsh[threadIdx.x] = S > 0.f ? gm / S : 0.f;
+        if (blockIdx.x == 0) ws.ghist[t * KMAX + threadIdx.x] = gm;
     }
     __syncthreads();
     float c1[K], c0[K], gS[K];
 #pragma unroll
-    for (int j = 0; j < K; ++j) { c1[j] = c1sh[j]; c0[j] = c0sh[j]; gS[j] = gSsh[j]; }
+    for (int j = 0; j < K; ++j) {
+        c1[j] = uniform(ws.chist[t * KMAX + j]);
+        c0[j] = uniform(ws.chist[(t - 1) * KMAX + j]);
+        gS[j] = uniform(gSsh[j]);
+    }
+    float* const gw = M.gw;
     float acc[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) acc[j] = 0.f;
-    uint64_t beg, end;
-    dense_range(M, beg, end);
-    for (uint64_t i = beg + threadIdx.x; i < end; i += D_THREADS) {
-        const uint32_t key = M.keys[i];
-        if (!key_finite(key, M.fmt)) continue;
-        const float v = key_value(key, M.fmt);
-        float a[K], dev[K], cm, gSm;
-        attn_row_dense<K>(v, c0, b.s2, a, c1, cm, gS, gSm);
-        const float direct = softmax_dev<K>(v, a, gS, c1, cm, gSm, dev);
-        float r = 0.f;
+    float o[4];
+    dense_for<4>(M,
+        [&](uint64_t i) { const float4 x = ld_f4(gw + i); o[0] = x.x; o[1] = x.y; o[2] = x.z; o[3] = x.w; },
+        [&](uint64_t i, uint32_t key, int u) {
+            if (!key_finite(key, fmt)) return;
+            const float v = key_value(key, fmt);
+            float a[K], dev[K], cm, xm, r = 0.f;
+            attn_row_dense<K>(v, c0, s2, a, c1, cm, xm);
+            const float direct = softmax_dev<K>(v, a, gS, c1, cm, 0.f, dev);
+            auto sum = [&](auto sgn) {
 #pragma unroll
-        for (int j = 0; j < K; ++j) {
-            const float dl = mul_sgn(a[j] * dev[j], v - c0[j]);
-            r += dl;
-            acc[j] += dl;
-        }
-        M.gw[i] += fmaf(-r, b.inv_tau, direct);
-    }
-    block_sum<K, D_THREADS>(acc, scratch, tot);
-    if (threadIdx.x < K) ws.dpart[(size_t)blockIdx.x * PSTRIDE + threadIdx.x] = tot[threadIdx.x];
+                for (int j = 0; j < K; ++j) {
+                    const float dl = sgn(a[j] * dev[j], v - c0[j]);
+                    r += dl;
+                    acc[j] += dl;
+                }
+            };
+            if (xm == 0.f) sum([](float y, float x) { return mul_sgn(y, x); });
+            else sum([](float y, float x) { return flip_sign(y, x); });
+            const float add = fmaf(-r, inv_tau, direct);
+            if (u >= 0) o[u & 3] += add;
+            else gw[i] += add;
+        },
+        [&](uint64_t i) { *reinterpret_cast<float4*>(gw + i) = make_float4(o[0], o[1], o[2], o[3]); });
+    dense_row<K>(acc, scratch, rsum, dense_part(ws, t & 1));
 }
 
-// One block.  b.t = 0 (after btop): gamma^(T) = dL/dC^(T) and E.  b.t = t in
-// T..1 (after biter t): gamma^(t-1) = dL/dC^(t-1); at t = 1 also dL/dC^(0).
+// One block, after iteration 1: dL/dC^(0).
 template <int K>
-__global__ void __launch_bounds__(1024) k_dense_bfin(BatchArgs b, int nrow) {
+__global__ void __launch_bounds__(D_THREADS) k_dense_bfin(BatchArgs b, int nrow) {
     EDKM_STAMP_ENTRY(b);
-    __shared__ float scratch[16 * PSTRIDE];
-    __shared__ float tot[2 * K];
+    __shared__ double red[D_WAVES * 2 * K], tot[2 * K < 4 ? 4 : 2 * K];
     const MatArgs& M = b.m[0];
     const Ws ws = carve_workspace(M.wsb, M.max_iter);
-    const int T = ws.st->teff;
-    const int t = b.t;
-    if (t == 0) {
-        reduce_dparts(ws.dpart, nrow, 0, 2 * K, scratch, tot);
-        if (threadIdx.x < K) {
-            ws.ghist[T * KMAX + threadIdx.x] = tot[threadIdx.x];
-            ws.ehist[threadIdx.x] = tot[K + threadIdx.x] * b.inv_tau;
-        }
-        return;
-    }
-    if (t > T) return;
-    reduce_dparts(ws.dpart, nrow, 0, K, scratch, tot);
-    if (threadIdx.x < K) {
-        const int j = threadIdx.x;
-        float gm = tot[j] * b.inv_tau;
-        if (t == T) gm += ws.ehist[j];
-        if (!(ws.shist[t * KMAX + j] > 0.f)) gm += ws.ghist[t * KMAX + j];
-        ws.ghist[(t - 1) * KMAX + j] = gm;
-        if (t == 1) M.gc[j] = gm;
-    }
+    const float gc = dense_gamma<K>(ws, 0, ws.st->teff, nrow, b.inv_tau, red, tot);
+    if (threadIdx.x < K) M.gc[threadIdx.x] = gc;
 }
 
 // ----------------------------------------------------------------------------
@@ -2536,7 +2646,6 @@ static hipError_t forward_dense_k(BatchArgs& b, uint32_t nwg, hipStream_t s, con
     for (int t = 1; t <= max_t; ++t) {
         b.t = t;
         EDKM_NPASS(PASS_DENSE_ITER, "k_dense_iter", k_dense_iter<K>, dim3(nwg), dim3(D_THREADS), b);
-        EDKM_LAUNCH("k_dense_fin", k_dense_fin<K>, dim3(1), dim3(1024), b, (int)nwg);
     }
     EDKM_LAUNCH("k_dense_out", k_dense_out<K>, dim3(nwg), dim3(D_THREADS), b);
     return hipSuccess;
@@ -2547,13 +2656,11 @@ static hipError_t backward_dense_k(BatchArgs& b, uint32_t nwg, hipStream_t s, co
                                    const PassEvents* ev) {
     const int max_t = b.m[0].max_iter;
     EDKM_LAUNCH("k_dense_btop", k_dense_btop<K>, dim3(nwg), dim3(D_THREADS), b);
-    b.t = 0;
-    EDKM_LAUNCH("k_dense_bfin", k_dense_bfin<K>, dim3(1), dim3(1024), b, (int)nwg);
     for (int t = max_t; t >= 1; --t) {
         b.t = t;
         EDKM_NPASS(PASS_DENSE_BITER, "k_dense_biter", k_dense_biter<K>, dim3(nwg), dim3(D_THREADS), b);
-        EDKM_LAUNCH("k_dense_bfin", k_dense_bfin<K>, dim3(1), dim3(1024), b, (int)nwg);
     }
+    EDKM_LAUNCH("k_dense_bfin", k_dense_bfin<K>, dim3(1), dim3(D_THREADS), b, (int)nwg);
     return hipSuccess;
 }
 
@@ -2650,6 +2757,7 @@ static_assert(MAGS == (NP_THREADS / 64) * 8 * 256, "window selection: 8 chunks o
 static_assert(fin_mags(FMT_FP16) % 4 == 0 && fin_mags(FMT_BF16) % 4 == 0,
               "window selection: a lane's 4 magnitudes are all finite or all not");
 static_assert(T_WG % 64 == 0, "table partial reduction: one lane per 64 workgroups");
+static_assert(D_WG * 32 <= 65536 && D_THREADS % 64 == 0, "dense partial rows");
 static_assert(T_WG * T_THREADS * T_KPT == NKEYS, "table blocks cover every pattern");
 
 }  // namespace edkm
