@@ -155,7 +155,9 @@ def _ptr(t, nbytes_elem=None, name="tensor", count=None):
 
 def _stream(stream):
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # the raw handle of torch's current stream; building the Stream object
+        # around it (torch.cuda.current_stream()) costs 15 us a call
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

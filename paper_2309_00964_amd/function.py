@@ -51,7 +51,7 @@ def _grad_in(grad_wt, w):
 def _outputs(w, plan, out_half):
     c_out = torch.empty(plan.k, dtype=torch.float32, device=w.device)
     wt = torch.empty(plan.n, dtype=w.dtype if out_half else torch.float32, device=w.device)
-    iters = torch.zeros(1, dtype=torch.int32, device=w.device)
+    iters = torch.empty(1, dtype=torch.int32, device=w.device)   # written by every forward
     return c_out, wt, iters
 
 
