@@ -1520,12 +1520,18 @@ __global__ void __launch_bounds__(NP_THREADS) k_keyed_grad(BatchArgs b) {
         const int bn = 64 - __clzll((unsigned long long)Slice<KW_U, 4>(M).bound(M) - 1);   // 2^bn >= weights added here
         const int emax = emax_sh;
         const int S = 181 - bn - emax;               // 2^(emax-126) * 2^S = 2^(55-bn)
+        // round(g 2^S), below 2^50 (bn >= 11), as the low bits of g 2^S + 1.5 2^52
+        // in double precision: one conversion, one fma and one subtraction.  (A
+        // conversion to a 64-bit integer takes about 12 instructions, which had
+        // bounded this mode: bf16 decoder layer, 16-bit gradients 194 -> 162 us,
+        // fp32 gradients 201 -> 194 us, the same sums.)
+        const double scale = ldexp(1.0, S), magic = 0x1.8p52;
         const uint32_t elim = (uint32_t)min(emax + 6, 0xFE);
         stream([&](uint32_t key, float gv) {
             const uint32_t d = (key & 0x7FFFu) - (uint32_t)lo;
             const uint32_t e = (__float_as_uint(gv) >> 23) & 0xFFu;
             if (d < (uint32_t)w && e <= elim) {
-                const long long q = __float2ll_rn(ldexpf(gv, S));
+                const long long q = __double_as_longlong(fma((double)gv, scale, magic)) - __double_as_longlong(magic);
                 atomicAdd(&lds[(key >> 15) * w + d], (unsigned long long)q);
             } else {
                 atomicAdd(&G[key], gv);
