@@ -33,7 +33,7 @@ constexpr int D_THREADS = 1024;
 // Device-side per-matrix state (in the workspace).
 struct DevState {
     int teff;            // iterations executed by the last forward
-    int conv;            // 1 once the eps criterion stopped the iteration
+    int conv;            // dense path: the launch that found the early stop, 0 while none has
     uint32_t nonfinite;  // 1 if any weight is Inf/NaN
     uint32_t num_unique; // occupied patterns
     int lo4, w4;         // 4-byte table window: magnitudes [lo4, lo4 + w4), both signs

@@ -2264,7 +2264,11 @@ __device__ __forceinline__ bool dense_centroids(const MatArgs& M, const Ws& ws, 
                                                 float* c0, double* red, double* tot, int* stop) {
     const bool lead = blockIdx.x == 0;
     DevState* st = ws.st;
-    const bool done = t > 1 && st->conv;
+    // conv: the launch that found the stop, 0 while none has.  That launch's first
+    // block sets it while others start; each takes 0 and t alike and comes to the
+    // same answer from the rows, so its threads never part here.
+    const int conv = st->conv;
+    const bool done = t > 1 && conv != 0 && conv < t;
     if (threadIdx.x == 0) *stop = 0;
     if (t > 1 && !done) dense_totals<2 * K>(dense_part(ws, (t - 1) & 1), (int)gridDim.x, red, tot);
     else __syncthreads();
@@ -2303,7 +2307,7 @@ __global__ void __launch_bounds__(D_THREADS) k_dense_iter(BatchArgs b) {
     const float s2 = b.s2;
     if (!dense_centroids<K>(M, ws, t, b.eps, csh, c0sh, red, tot, &stop)) {
         // max_j |C^(t-1) - C^(t-2)| <= eps now or before
-        if (blockIdx.x == 0 && threadIdx.x == 0 && !ws.st->conv) { ws.st->teff = t - 1; ws.st->conv = 1; }
+        if (blockIdx.x == 0 && threadIdx.x == 0 && !ws.st->conv) { ws.st->teff = t - 1; ws.st->conv = t; }
         return;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0 && t == 1) ws.st->conv = 0;
@@ -2340,7 +2344,7 @@ __global__ void __launch_bounds__(D_THREADS) k_dense_out(BatchArgs b) {
     __shared__ int stop;
     const MatArgs& M = b.m[0];
     const Ws ws = carve_workspace(M.wsb, M.max_iter);
-    const bool conv = ws.st->conv;   // by an iteration's launch: T is in the state
+    const bool conv = ws.st->conv != 0;   // by an iteration's launch: T is in the state
     int T = M.max_iter;
     if (conv) {
         T = ws.st->teff;
