@@ -206,13 +206,14 @@ __device__ __forceinline__ void attn_row_sel(float v, const float (&c)[K], float
 // as in attn_row_sel (nearest centroid, first on ties).
 constexpr float DENSE_FAST_X = 256.f;
 
-// The row alone, unnormalised, with the factor it returns.
+// The row alone, unnormalised, with the factor it returns, and the nearest
+// centroid's distance xm.
 template <int K>
-__device__ __forceinline__ float attn_row_dense_near(float v, const float (&c)[K], float s2, float (&a)[K]) {
+__device__ __forceinline__ float attn_row_dense_near(float v, const float (&c)[K], float s2, float (&a)[K], float& xm) {
     float d[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) d[j] = v - c[j];
-    float xm = fabsf(d[0]);
+    xm = fabsf(d[0]);
 #pragma unroll
     for (int j = 1; j < K; ++j) xm = fminf(xm, fabsf(d[j]));   // two to an instruction (v_min3)
     const float off = xm * s2;
@@ -289,7 +290,7 @@ __device__ __forceinline__ float centroid_dev(const float (&a)[K], const float (
 // written around the reference cm = c1_m, gm = gS_m (m the nearest centroid) as
 //   dev_j = (gS_j - gm - db)(v - cm) - (gS_j (c1_j - cm) - hb),
 //   db = sum_i a_i (gS_i - gm),  hb = sum_i a_i gS_i (c1_i - cm)
-// (any gm gives the same; the dense path passes 0),
+// (any gm gives the same),
 // which subtracts neither two terms of size |v| nor, for a nearly one-hot row,
 // two nearly equal gS (their rounding error, times |v| / tau, was dL/dw's
 // largest for weights far from zero).  Returns sum_i a_i gS_i = gm + db.
@@ -2189,13 +2190,17 @@ __global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, true> / 256)) 
 // ----------------------------------------------------------------------------
 // dense (non-uniquified) comparison path: one attention row per weight
 
-// Bound by VALU issue (about 10 instructions a map entry in the iterations, 25
-// in the backward's).  4096x4096 at 3 bits: the whole step 951 -> 706 us with
+// Bound by VALU issue.  4096x4096 at 3 bits: the whole step 951 -> 706 us with
 // one 1024-thread block a CU that forms the centroids itself from the previous
 // launch's rows (11 single-block launches less), keys and gradients loaded 4 or
 // 8 to a thread, the nearest distance by minima (k_dense_iter 51 -> 40 us), a
 // Newton reciprocal for the division, and d|x|/dx at 0 looked at only where a
-// weight lies on a centroid (k_dense_biter 94 -> 86 us).
+// weight lies on a centroid (k_dense_biter 94 -> 86 us); then 611 us with the
+// softmax Jacobian from p_j = gS_j (v - C_j) as it stands (k_dense_biter 85 ->
+// 65 us).  Taking it around the nearest centroid, as the table phase does, needs
+// a select of that centroid per entry and two more products, and is no more
+// exact here: both round at |gS| |v - C| (dL/dw against 64 bits 4.5e-7 at 4
+// bits and 2.6e-7 at 2 bits with outliers, either way).
 
 // The weights of a block's chunk: fn(i, key, u) for each, in groups of GW
 // consecutive ones per thread (u: place in the group), loaded together where
@@ -2322,7 +2327,8 @@ __global__ void __launch_bounds__(D_THREADS) k_dense_iter(BatchArgs b) {
             if (!key_finite(key, fmt)) return;
             const float v = key_value(key, fmt);
             float a[K];
-            const float r = attn_row_dense_near<K>(v, c, s2, a);
+            float xm;
+            const float r = attn_row_dense_near<K>(v, c, s2, a, xm);
             const float rv = r * v;
 #pragma unroll
             for (int j = 0; j < K; ++j) {
@@ -2378,7 +2384,8 @@ __global__ void __launch_bounds__(D_THREADS) k_dense_out(BatchArgs b) {
             float wv;
             float a[K];
             if (key_finite(key, fmt)) {
-                const float r = attn_row_dense_near<K>(key_value(key, fmt), c0, s2, a);
+                float xm;
+                const float r = attn_row_dense_near<K>(key_value(key, fmt), c0, s2, a, xm);
                 wv = 0.f;
 #pragma unroll
                 for (int j = 0; j < K; ++j) {
@@ -2512,19 +2519,27 @@ __global__ void __launch_bounds__(D_THREADS) k_dense_biter(BatchArgs b) {
         [&](uint64_t i, uint32_t key, int u) {
             if (!key_finite(key, fmt)) return;
             const float v = key_value(key, fmt);
-            float a[K], dev[K], cm, xm, r = 0.f;
-            attn_row_dense<K>(v, c0, s2, a, c1, cm, xm);
-            const float direct = softmax_dev<K>(v, a, gS, c1, cm, 0.f, dev);
+            // dev_j = p_j - sum_i a_i p_i with p_j = gS_j (v - C^(t)_j); the row's
+            // factor q goes into dev, and d|x|/dx into a_j's sign
+            float a[K], p[K], xm, gb = 0.f, pb = 0.f, r = 0.f;
+            const float q = attn_row_dense_near<K>(v, c0, s2, a, xm);
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                p[j] = gS[j] * (v - c1[j]);
+                gb = fmaf(a[j], gS[j], gb);
+                pb = fmaf(a[j], p[j], pb);
+            }
+            const float direct = gb * q, mean = pb * q * q;
             auto sum = [&](auto sgn) {
 #pragma unroll
                 for (int j = 0; j < K; ++j) {
-                    const float dl = sgn(a[j] * dev[j], v - c0[j]);
-                    r += dl;
-                    acc[j] += dl;
+                    const float sa = sgn(a[j], v - c0[j]), dev = fmaf(p[j], q, -mean);
+                    r = fmaf(sa, dev, r);
+                    acc[j] = fmaf(sa, dev, acc[j]);
                 }
             };
             if (xm == 0.f) sum([](float y, float x) { return mul_sgn(y, x); });
-            else sum([](float y, float x) { return flip_sign(y, x); });
+            else sum([](float y, float x) { return copysignf(y, x); });   // y >= 0
             const float add = fmaf(-r, inv_tau, direct);
             if (u >= 0) o[u & 3] += add;
             else gw[i] += add;
