@@ -2086,7 +2086,8 @@ __global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, true> / 256)) 
         float x[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            const int k = q + i * T_WG, y = min(k / max(nx, 1), chunks);
+            // (no finite weight: no window, nx = 0, and the global G's rows alone)
+            const int k = q + i * T_WG, y = k < chunks * nx ? k / nx : chunks;
             x[i] = k < chunks * nx + MERGE_X && threadIdx.x < 2 * K
                        ? ws.tx[((size_t)y * MERGE_X + (k - y * nx)) * (2 * K) + threadIdx.x] : 0.f;
         }
