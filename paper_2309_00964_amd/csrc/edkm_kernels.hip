@@ -2196,12 +2196,16 @@ __global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, true> / 256)) 
 // launch's rows (11 single-block launches less), keys and gradients loaded 4 or
 // 8 to a thread, the nearest distance by minima (k_dense_iter 51 -> 40 us), a
 // Newton reciprocal for the division, and d|x|/dx at 0 looked at only where a
-// weight lies on a centroid (k_dense_biter 94 -> 86 us); then 611 us with the
-// softmax Jacobian from p_j = gS_j (v - C_j) as it stands (k_dense_biter 85 ->
-// 65 us).  Taking it around the nearest centroid, as the table phase does, needs
-// a select of that centroid per entry and two more products, and is no more
-// exact here: both round at |gS| |v - C| (dL/dw against 64 bits 4.5e-7 at 4
-// bits and 2.6e-7 at 2 bits with outliers, either way).
+// weight lies on a centroid (k_dense_biter 94 -> 86 us); then 635 us with the
+// softmax Jacobian from p_j = gS_j (v - C_j) and its mean over the row, taken
+// twice (k_dense_biter 85 -> 73 us).  Around the nearest centroid, as the table
+// phase takes it, it needs a select of that centroid per entry and two more
+// products.  From one mean alone it took 65 us (the step 611), but the dominant
+// entry of a nearly one-hot row is then the difference of two numbers of size
+// |gS| |v - C|, divided by tau: at tau = 2e-3 the largest error of dL/dw, through
+// the centroids, was 1.8e-6 to 7.1e-6 of the largest entry instead of 2.5e-7 to
+// 4.5e-7 (weights up to ten times wider than the bulk, 2 to 16 centroids), at tau
+// = 1e-4 the rel-L2 4.2e-7 to 5.3e-7 instead of 0.8e-7 to 2.1e-7.
 
 // The weights of a block's chunk: fn(i, key, u) for each, in groups of GW
 // consecutive ones per thread (u: place in the group), loaded together where
@@ -2520,9 +2524,10 @@ __global__ void __launch_bounds__(D_THREADS) k_dense_biter(BatchArgs b) {
         [&](uint64_t i, uint32_t key, int u) {
             if (!key_finite(key, fmt)) return;
             const float v = key_value(key, fmt);
-            // dev_j = p_j - sum_i a_i p_i with p_j = gS_j (v - C^(t)_j); the row's
-            // factor q goes into dev, and d|x|/dx into a_j's sign
-            float a[K], p[K], xm, gb = 0.f, pb = 0.f, r = 0.f;
+            // dev_j = p_j - sum_i a_i p_i with p_j = gS_j (v - C^(t)_j), the mean
+            // taken twice: first of p, then of what is left of p around that
+            // mean.  The row's factor q goes into dev, d|x|/dx into a_j's sign
+            float a[K], p[K], xm, gb = 0.f, pb = 0.f, rb = 0.f, r = 0.f;
             const float q = attn_row_dense_near<K>(v, c0, s2, a, xm);
 #pragma unroll
             for (int j = 0; j < K; ++j) {
@@ -2530,7 +2535,13 @@ __global__ void __launch_bounds__(D_THREADS) k_dense_biter(BatchArgs b) {
                 gb = fmaf(a[j], gS[j], gb);
                 pb = fmaf(a[j], p[j], pb);
             }
-            const float direct = gb * q, mean = pb * q * q;
+            const float direct = gb * q, m0 = pb * q;
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                p[j] -= m0;
+                rb = fmaf(a[j], p[j], rb);
+            }
+            const float mean = rb * q * q;
             auto sum = [&](auto sgn) {
 #pragma unroll
                 for (int j = 0; j < K; ++j) {
