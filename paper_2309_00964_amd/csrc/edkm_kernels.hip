@@ -159,6 +159,7 @@ template <int K>
 __device__ __forceinline__ float attn_row_sel_un(float v, const float (&c)[K], float s2, float (&a)[K],
                                                  const float (&e)[K], float& em, const float (&f)[K],
                                                  float& fm) {
+#pragma clang fp contract(off)
     float t[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) t[j] = v - c[j];
@@ -185,6 +186,7 @@ __device__ __forceinline__ float attn_row_sel_un(float v, const float (&c)[K], f
 template <int K>
 __device__ __forceinline__ void attn_row_sel(float v, const float (&c)[K], float s2, float (&a)[K],
                                              const float (&e)[K], float& em, const float (&f)[K], float& fm) {
+#pragma clang fp contract(off)
     const float r = attn_row_sel_un<K>(v, c, s2, a, e, em, f, fm);
 #pragma unroll
     for (int j = 0; j < K; ++j) a[j] *= r;
@@ -277,6 +279,7 @@ __device__ __forceinline__ void attn_row_dense(float v, const float (&c)[K], flo
 template <int K>
 __device__ __forceinline__ float centroid_dev(const float (&a)[K], const float (&c1)[K], float c1m,
                                               float (&d)[K]) {
+#pragma clang fp contract(off)
     float dt = 0.f;
 #pragma unroll
     for (int j = 0; j < K; ++j) dt = fmaf(a[j], c1[j] - c1m, dt);
@@ -297,6 +300,7 @@ __device__ __forceinline__ float centroid_dev(const float (&a)[K], const float (
 template <int K>
 __device__ __forceinline__ float softmax_dev(float v, const float (&a)[K], const float (&gS)[K],
                                              const float (&c1)[K], float cm, float gm, float (&dev)[K]) {
+#pragma clang fp contract(off)
     float db = 0.f, hb = 0.f;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
@@ -1127,9 +1131,14 @@ __global__ void __launch_bounds__(NP_THREADS) k_window(BatchArgs b) {
 // cost 10 us and more: it writes back and invalidates the XCDs' L2s.)
 //
 // No block relies on another one running.  A block that has waited XW_WAIT
-// computes the rows it still misses itself, with the same code and therefore
-// the same bits, so every wait ends whatever else occupies the GPU; a block
-// that starts late finds the rows it needs already there.
+// computes the rows it still misses itself, so every wait ends whatever else
+// occupies the GPU; a block that starts late finds the rows it needs already
+// there.  A row's bits must not depend on who computes it (blocks may see rows
+// of either origin, and decide the early stop from them), but its code is
+// inlined once for each of a block's virtual blocks and once more for the rows
+// of others: so nothing is left to the compiler's choice there.  Products are
+// added by a written fmaf, and contraction of others is off in these kernels
+// and in the functions that they share.
 //
 // Every row word is XW_EMPTY when a phase starts: the forward's rows are
 // emptied by k_init_zero and again by k_gather_wt, the launch after the phase
@@ -1140,6 +1149,17 @@ __global__ void __launch_bounds__(NP_THREADS) k_window(BatchArgs b) {
 #define EDKM_XW_WAIT 2000
 #endif
 constexpr long long XW_WAIT = EDKM_XW_WAIT;  // wall-clock ticks (100 MHz): 20 us
+
+// Test builds: every second block of a table phase starts this many ticks late.
+#ifndef EDKM_XW_LATE
+#define EDKM_XW_LATE 0
+#endif
+__device__ __forceinline__ void xw_late() {
+    if constexpr (EDKM_XW_LATE > 0) {
+        const long long t0 = wall_clock64();
+        while ((blockIdx.x & 1u) && wall_clock64() - t0 < EDKM_XW_LATE) {}
+    }
+}
 
 // Blocks of one launch, at most: as many as the GPU's 256 CUs hold at a time, 4
 // a CU (128 registers a thread), or 3 or 2 where the backward at k = 16 needs
@@ -1223,10 +1243,12 @@ __device__ __forceinline__ uint32_t table_key(int q, int r) {
 // clears G.  Grid (T_WG / VB, count).
 template <int K, int VB>
 __global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, false> / 256)) k_fwd_table(BatchArgs b) {
+#pragma clang fp contract(off)
     __shared__ float red[BLOCK_TOTAL_LDS(2 * K)];
     __shared__ double cols[8 * K];
     __shared__ float c1sh[K], c0sh[K];   // C^(t), C^(t-1)
     __shared__ int stop, miss;
+    xw_late();
     const MatArgs& M = b.m[blockIdx.y];
     const float* c_in = M.c_in;
     float* const c_out = M.c_out;
@@ -1274,9 +1296,8 @@ __global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, false> / 256))
                 const float nr = (float)n[r] * attn_row_sel_un<K>(v, c, s2, a, c, unused, c, unused);
 #pragma unroll
                 for (int j = 0; j < K; ++j) {
-                    const float w = nr * a[j];
-                    acc[j] += w;
-                    acc[K + j] = fmaf(w, v, acc[K + j]);
+                    acc[j] = fmaf(nr, a[j], acc[j]);
+                    acc[K + j] = fmaf(nr * a[j], v, acc[K + j]);
                 }
             }
             return block_total<2 * K>(acc, red);
@@ -2052,11 +2073,13 @@ __global__ void __launch_bounds__(MERGE_THREADS) k_grad_top(BatchArgs b) {
 // k_gather_grad forms dL/dC^(0).  Writes R beside H.  Grid as k_fwd_table's.
 template <int K, int VB>
 __global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, true> / 256)) k_bwd_table(BatchArgs b, int chunks) {
+#pragma clang fp contract(off)
     __shared__ float red[BLOCK_TOTAL_LDS(K)];
     constexpr int NC = K < 4 ? 4 : K;   // words of a row (unused columns hold 0)
     __shared__ double cols[8 * K];
     __shared__ float gSsh[K], c1sh[K], c0sh[K];
     __shared__ int miss;
+    xw_late();
     const MatArgs& M = b.m[blockIdx.y];
     // the arguments, in one wait
     const int max_iter = M.max_iter, fmt = M.fmt;
@@ -2117,7 +2140,7 @@ __global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, true> / 256)) 
                 gm = g_top;
             } else {
                 float x = (float)Cols<NC>::total(cols, jk) * inv_tau;
-                if (t + 1 == T) x += e_top * inv_tau;
+                if (t + 1 == T) x = fmaf(e_top, inv_tau, x);
                 if (!(hS1 > 0.f)) x += gm;
                 gm = x;
             }
