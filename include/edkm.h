@@ -136,7 +136,7 @@ edkm_status edkm_init_unique(edkm_plan* plan, const uint16_t* w_bits,
  *   w_bits     device, n patterns; must be the buffer given to init_unique
  *   tau        > 0, finite;  eps >= 0 (0: exactly max_iter iterations)
  *   c_in       device float[k]: C^(0)
- *   c_out      device float[k]: C^(T)
+ *   c_out      device float[k]: C^(T); may be c_in
  *   w_tilde    device, n outputs: float, or, if out_half = 1, 16-bit floats
  *              of the plan's weight format (fp16 or bf16 bits, uint16; round to
  *              nearest even)

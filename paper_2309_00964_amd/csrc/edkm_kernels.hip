@@ -1251,12 +1251,11 @@ __global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, false> / 256))
     xw_late();
     const MatArgs& M = b.m[blockIdx.y];
     const float* c_in = M.c_in;
-    float* const c_out = M.c_out;
     int32_t* const iters_out = M.iters_out;
     const int max_iter = M.max_iter, fmt = M.fmt;
     const float eps = b.eps, s2 = b.s2, inv_tau = b.inv_tau;
     // the arguments, in one wait
-    asm volatile("" ::"s"(c_in), "s"(c_out), "s"(iters_out), "s"(max_iter), "s"(fmt), "s"(eps), "s"(s2),
+    asm volatile("" ::"s"(c_in), "s"(iters_out), "s"(max_iter), "s"(fmt), "s"(eps), "s"(s2),
                  "s"(inv_tau), "s"(M.wsb));
     const Ws ws = carve_workspace(M.wsb, M.max_iter);
     const bool lead = blockIdx.x == 0;
@@ -1327,8 +1326,9 @@ __global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, false> / 256))
     EDKM_STAMP_BEGIN(b, b.t);
     if (lead) {
         if (threadIdx.x < K) {
-            c_out[threadIdx.x] = c1sh[threadIdx.x];
-            ws.cfin[threadIdx.x] = c0sh[threadIdx.x];        // for k_grad_top, which does not know T
+            // for k_grad_top, which does not know T, and k_gather_wt, which writes
+            // c_out: it may be c_in, which a block that starts late reads yet
+            ws.cfin[threadIdx.x] = c0sh[threadIdx.x];
             ws.cfin[KMAX + threadIdx.x] = c1sh[threadIdx.x];
         }
         if (threadIdx.x == 0) {
@@ -1374,7 +1374,8 @@ __global__ void __launch_bounds__(NP_THREADS) k_gather_wt(BatchArgs b) {
     const uint32_t wl = blockIdx.x - b.wg_begin[mi];
     const int lo = ws.st->lo4, w = ws.st->w4;
     const float* tab = ws.tab;
-    // the table phase is over: empty its rows for another forward
+    // the table phase is over: c_out, and its rows emptied for another forward
+    if (wl == 0 && threadIdx.x < (uint32_t)M.k) M.c_out[threadIdx.x] = ws.cfin[KMAX + threadIdx.x];
     for (uint32_t i = wl * NP_THREADS + threadIdx.x; i < (uint32_t)(M.max_iter * T_WG * 2 * M.k);
          i += M.wg_count * NP_THREADS)
         ws.fx[i] = XW_EMPTY;

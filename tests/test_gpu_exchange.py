@@ -45,6 +45,8 @@ def test_rows_computed_by_waiting_blocks_have_the_same_bits(tmp_path):
     want = child(build.OUT, tmp_path / "product.npz")
     got = child(build.OUT_EXCHANGE, tmp_path / "exchange.npz")
     assert sorted(want) == sorted(got)
+    # (the child's last forward updates the centroids in place: a block that
+    # starts late still has to read C^(0))
     assert len({int(v[0]) for k, v in want.items() if k.startswith("11.it")}) > 1    # early stops differ
     bad = [k for k in want if not same_bits(want[k], got[k])]
     assert not bad, bad
@@ -72,3 +74,29 @@ def test_a_batch_has_the_bits_of_single_calls(case):
     for name in res[0]:
         for i in range(count):
             assert same_bits(res[0][name][i].cpu().numpy(), res[1][name][i].cpu().numpy()), (name, i)
+
+
+@pytest.mark.parametrize("dense", [False, True])
+def test_centroids_updated_in_place(dense):
+    """c_out may be c_in: the same bits as with a buffer of its own."""
+    print("[gpu-case] exchange: centroids in place", dense, flush=True)
+    (n,), (keys,), (c0,), (g,) = exchange_child.case_inputs(3, 1, "fp16")
+    res = []
+    for in_place in (False, True):
+        o = exchange_child.outputs([n], 8)
+        c_in, c_out = c0.clone(), o["c"][0]
+        if in_place:
+            o["c"][0] = c_out = c_in
+        plan = edkm.Plan(n, 3, 5)
+        if dense:
+            edkm.forward_dense(plan, keys, inputs.TAU, 0.0, c_in, c_out, o["wt"][0], False, o["it"][0])
+            edkm.backward_dense(plan, keys, g, o["gw"][0], o["gc"][0])
+        else:
+            edkm.init_unique(plan, keys)
+            edkm.forward(plan, keys, inputs.TAU, 0.0, c_in, c_out, o["wt"][0], False, o["it"][0])
+            edkm.backward(plan, keys, g, o["gw"][0], o["gc"][0])
+        torch.cuda.synchronize()
+        res.append(o)
+    assert not same_bits(res[1]["c"][0].cpu().numpy(), c0.cpu().numpy())
+    for name in res[0]:
+        assert same_bits(res[0][name][0].cpu().numpy(), res[1][name][0].cpu().numpy()), name
