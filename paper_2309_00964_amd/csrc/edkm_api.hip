@@ -30,7 +30,10 @@ struct PlanImpl {
     const uint16_t* keys;   // key buffer of the current sequence
     float tau;
     float eps;
-    int32_t stale_rows;      // 1: a forward failed between its launches, its exchange rows may not be empty
+    // 1 from a forward that failed on (it may have ended between its launches, its
+    // exchange rows full): forwards empty them first.  No later success takes it
+    // back, since a captured call succeeds without having run.
+    int32_t stale_rows;
     int32_t hip_code;        // last HIP failure on this plan (0 if none)
     const char* hip_step;    // the launch or runtime call that failed
     PassEvents ev;           // caller's timing events (diagnostics), null when unset
@@ -253,7 +256,6 @@ edkm_status edkm_init_unique_batch(int count, edkm_plan* const* plans,
         }
         PlanImpl* P = impl(plans[i]);
         P->stage = bad ? PLANNED : COUNTED;
-        P->stale_rows = 0;   // k_init_zero emptied them
         P->keys = bad ? nullptr : w_bits[i];
         any_bad = any_bad || bad;
     }
@@ -297,9 +299,8 @@ edkm_status edkm_forward_batch(int count, edkm_plan* const* plans, const uint16_
         int max_t = 0;
         for (int i = 0; i < cnt; ++i) {
             const int q = first + i;
-            PlanImpl* P = impl(plans[q]);
+            const PlanImpl* P = impl(plans[q]);
             stale = stale || P->stale_rows;
-            P->stale_rows = 1;
             MatArgs& M = b.m[i];
             fill_mat(M, P, w_bits[q]);
             M.c_in = c_in[q];
@@ -313,8 +314,10 @@ edkm_status edkm_forward_batch(int count, edkm_plan* const* plans, const uint16_
         const uint32_t grid = partition(b, np_budget());
         const char* where = "";
         const hipError_t e = launch_forward(b, grid, max_t, stale, stream, &where, &impl(plans[first])->ev);
-        if (e != hipSuccess) return hip_fail(plans, first, cnt, e, where);
-        for (int i = 0; i < cnt; ++i) impl(plans[first + i])->stale_rows = 0;
+        if (e != hipSuccess) {
+            for (int i = 0; i < cnt; ++i) impl(plans[first + i])->stale_rows = 1;
+            return hip_fail(plans, first, cnt, e, where);
+        }
         return EDKM_OK;
     });
     if (st != EDKM_OK) return st;

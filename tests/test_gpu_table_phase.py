@@ -3,6 +3,8 @@ virtual block, two virtual blocks per block and several launches give, bit for
 bit in the forward, what single calls give (which one launch of 64 blocks
 computes), and a forward repeated after one init_unique starts from clean
 exchange rows."""
+import os
+import subprocess
 import sys
 
 import numpy as np
@@ -71,3 +73,78 @@ def test_forward_repeated_after_one_init():
     torch.cuda.synchronize()
     assert_close(gw.cpu().numpy(), s["grad_w"].cpu().numpy(), 1e-5, "grad_w")
     assert_close(gc.cpu().numpy(), s["grad_c"].cpu().numpy(), 1e-5, "grad_c")
+
+
+def forward_after_a_failed_one():
+    import ctypes
+    hip = ctypes.CDLL([x for x in edkm._hip_runtimes()][0])
+    n, iters, k = 20_011, 4, 8
+    kh = inputs.fp16_weights(n, 730)
+    keys = torch.from_numpy(kh.view(np.int16)).to(DEV)
+    c0 = torch.from_numpy(inputs.quantile_init(kh, k)).to(DEV)
+    co, wt = torch.empty(k, device=DEV), torch.empty(n, device=DEV)
+    plan = edkm.Plan(n, 3, iters, workspace=torch.zeros(edkm.workspace_bytes(n, 3, iters), dtype=torch.uint8, device=DEV))
+    want = run(keys, c0, 3, inputs.TAU, iters)
+    edkm.init_unique(plan, keys)
+    # the rows: the words that init_unique emptied (all ones) in a workspace of zeros
+    words = plan.workspace.view(torch.int32)
+    at = torch.nonzero(words == -1).flatten()
+    assert at.numel() == iters * 64 * 2 * k and int(at[-1] - at[0]) == at.numel() - 1
+    rows = words[int(at[0]):int(at[-1]) + 1]
+
+    def forward(stream):
+        co.zero_(), wt.zero_()
+        torch.cuda.synchronize()
+        edkm.forward(plan, keys, inputs.TAU, 0.0, c0, co, wt, stream=stream)
+
+    def check(what):
+        torch.cuda.synchronize()
+        assert torch.equal(co, want["c_out"]) and torch.equal(wt, want["w_tilde"]), what
+        assert bool((rows == -1).all())
+
+    s = torch.cuda.Stream()
+    forward(s)
+    check("before")
+    print("[gpu-case] forward into an invalidated capture", flush=True)
+    raw, graph = ctypes.c_void_p(), ctypes.c_void_p()      # a stream of its own: it stays invalidated
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(raw), 1) == 0
+    assert hip.hipStreamBeginCapture(raw, 2) == 0          # relaxed
+    assert hip.hipStreamSynchronize(raw) != 0              # not allowed: invalidates the capture
+    with pytest.raises(edkm.EdkmError) as e:
+        edkm.forward(plan, keys, inputs.TAU, 0.0, c0, co, wt, stream=raw.value)
+    assert e.value.status == edkm.ERR_HIP
+    assert hip.hipStreamEndCapture(raw, ctypes.byref(graph)) != 0
+    hip.hipGetLastError()
+
+    print("[gpu-case] forward on full rows", flush=True)
+    full = torch.linspace(0.5, 2.0, rows.numel(), device=DEV).view(torch.int32)
+    rows.copy_(full)
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        edkm.forward(plan, keys, inputs.TAU, 0.0, c0, co, wt)
+    forward(s)                                             # the graph has not run
+    check("eager")
+    for rep in range(3):
+        rows.copy_(full)
+        co.zero_(), wt.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        check("replay %d" % rep)
+    print("failed forward ok", flush=True)
+
+
+def test_forward_after_one_that_failed_between_its_launches():
+    """A failed forward may leave its exchange rows full.  The failure is a launch
+    into a capture that has been invalidated (in a process of its own); what the
+    launches before it would have left is written into the rows by hand.  A later
+    forward empties them first, eagerly and captured, and a captured one that has
+    not been replayed does not stand in for that."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, os.path.abspath(__file__)], cwd=root, capture_output=True, text=True,
+                       timeout=110, env=dict(os.environ, PYTHONPATH=root))
+    assert r.returncode == 0 and "failed forward ok" in r.stdout, (r.stdout[-1000:], r.stderr[-3000:])
+
+
+if __name__ == "__main__":
+    forward_after_a_failed_one()
