@@ -795,14 +795,20 @@ constexpr uint32_t XW_EMPTY = 0xFFFFFFFFu;
 // ----------------------------------------------------------------------------
 // init_unique: zero, histogram, partial merge, window selection
 
+// Empties the forward's exchange rows, those of all max_iter iterations.
+__device__ __forceinline__ void empty_all_rows(const MatArgs& M, const Ws& ws) {
+    const int n4 = M.max_iter * T_WG * 2 * M.k / 4;
+    for (int i = blockIdx.x * T_THREADS + threadIdx.x; i < n4; i += gridDim.x * T_THREADS)
+        reinterpret_cast<uint4*>(ws.fx)[i] = uint4{XW_EMPTY, XW_EMPTY, XW_EMPTY, XW_EMPTY};
+}
+
 __global__ void __launch_bounds__(T_THREADS) k_init_zero(BatchArgs b) {
     EDKM_STAMP_ENTRY(b);
     const MatArgs& M = b.m[blockIdx.y];
     const Ws ws = carve_workspace(M.wsb, M.max_iter);
     for (int u = blockIdx.x * T_THREADS + threadIdx.x; u < NKEYS; u += gridDim.x * T_THREADS)
         ws.counts[u] = 0u;
-    for (int i = blockIdx.x * T_THREADS + threadIdx.x; i < M.max_iter * T_WG * 2 * M.k; i += gridDim.x * T_THREADS)
-        ws.fx[i] = XW_EMPTY;
+    empty_all_rows(M, ws);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         DevState* st = ws.st;
         st->teff = 0;
@@ -818,8 +824,7 @@ __global__ void __launch_bounds__(T_THREADS) k_empty_rows(BatchArgs b) {
     EDKM_STAMP_ENTRY(b);
     const MatArgs& M = b.m[blockIdx.y];
     const Ws ws = carve_workspace(M.wsb, M.max_iter);
-    for (int i = blockIdx.x * T_THREADS + threadIdx.x; i < M.max_iter * T_WG * 2 * M.k; i += gridDim.x * T_THREADS)
-        ws.fx[i] = XW_EMPTY;
+    empty_all_rows(M, ws);
 }
 
 // Pattern histogram.  Magnitudes [0, W4) of both signs (|w| < 16) count in
@@ -1141,9 +1146,9 @@ __global__ void __launch_bounds__(NP_THREADS) k_window(BatchArgs b) {
 // and in the functions that they share.
 //
 // Every row word is XW_EMPTY when a phase starts: the forward's rows are
-// emptied by k_init_zero and again by k_gather_wt, the launch after the phase
-// (a forward may be repeated after one init_unique); the backward's by
-// k_keyed_grad, two launches before it.
+// emptied by k_init_zero and those it used again by k_gather_wt, the launch after
+// the phase (a forward may be repeated after one init_unique); the ones that the
+// backward will use by k_keyed_grad, two launches before it.
 
 #ifndef EDKM_XW_WAIT
 #define EDKM_XW_WAIT 2000
@@ -1376,7 +1381,7 @@ __global__ void __launch_bounds__(NP_THREADS) k_gather_wt(BatchArgs b) {
     const float* tab = ws.tab;
     // the table phase is over: c_out, and its rows emptied for another forward
     if (wl == 0 && threadIdx.x < (uint32_t)M.k) M.c_out[threadIdx.x] = ws.cfin[KMAX + threadIdx.x];
-    for (uint32_t i = wl * NP_THREADS + threadIdx.x; i < (uint32_t)(M.max_iter * T_WG * 2 * M.k);
+    for (uint32_t i = wl * NP_THREADS + threadIdx.x; i < (uint32_t)(ws.st->teff * T_WG * 2 * M.k);
          i += M.wg_count * NP_THREADS)
         ws.fx[i] = XW_EMPTY;
     fill_lds<2 * W4, NP_THREADS>(tw, tab, 2 * w, [&](int i) {
@@ -1496,11 +1501,14 @@ __global__ void __launch_bounds__(NP_THREADS) k_keyed_grad(BatchArgs b) {
         for (int i = threadIdx.x; i < n16; i += NP_THREADS) reinterpret_cast<uint4*>(lds)[i] = uint4{0u, 0u, 0u, 0u};
     }
     if (threadIdx.x == 0) { emax_sh = 0; esum_sh = 0; ecnt_sh = 0; }
-    // Empty the rows that the backward's table phase exchanges; the previous
+    // Empty the rows that the backward's table phase exchanges (those of its T
+    // iterations, then the first sums' behind all max_iter of them); the previous
     // backward's reads of them are over.
-    for (uint32_t i = wl * NP_THREADS + threadIdx.x; i < (uint32_t)(T_WG * (M.max_iter * max(M.k, 4) + 2 * M.k));
-         i += M.wg_count * NP_THREADS)
-        ws.bx[i] = XW_EMPTY;
+    {
+        const uint32_t nc = T_WG * max(M.k, 4), it = st->teff * nc, n = it + T_WG * 2 * M.k;
+        for (uint32_t i = wl * NP_THREADS + threadIdx.x; i < n; i += M.wg_count * NP_THREADS)
+            ws.bx[i < it ? i : i - it + M.max_iter * nc] = XW_EMPTY;
+    }
     __syncthreads();
     {   // sample: 64 consecutive values per wave, the waves' runs spread over the
         // matrix (one value per thread at scattered indices had cost a 128-byte

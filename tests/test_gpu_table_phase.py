@@ -75,6 +75,33 @@ def test_forward_repeated_after_one_init():
     assert_close(gc.cpu().numpy(), s["grad_c"].cpu().numpy(), 1e-5, "grad_c")
 
 
+@pytest.mark.parametrize("max_iter", [9, 1024])
+def test_rows_of_the_iterations_run_are_emptied(max_iter):
+    """One plan, forwards that stop after many, one, several iterations, a backward
+    after each (twice after the last): every step gives a fresh plan's bits."""
+    n = 15_001                                        # one workgroup per N-sized pass: no atomic's order matters
+    kh = inputs.fp16_weights(n, 740)
+    keys = torch.from_numpy(kh.view(np.int16)).to(DEV)
+    c0 = torch.from_numpy(inputs.quantile_init(kh, 16)).to(DEV)
+    g = torch.from_numpy(inputs.upstream_grad(n, 741)).to(DEV)
+    plan = edkm.Plan(n, 4, max_iter, device=DEV)
+    co, wt, gw, gc = (torch.empty(m, device=DEV) for m in (16, n, n, 16))
+    it = torch.zeros(1, dtype=torch.int32, device=DEV)
+    edkm.init_unique(plan, keys)
+    seen = []
+    for eps in (2e-4, 1.0, 1e-3, 2e-4):
+        print("[gpu-case] rows emptied", max_iter, eps, flush=True)
+        edkm.forward(plan, keys, inputs.TAU, eps, c0, co, wt, False, it)
+        s = run(keys, c0, 4, inputs.TAU, max_iter, eps=eps, grad=g)
+        for rep in range(2 if len(seen) == 3 else 1):
+            edkm.backward(plan, keys, g, gw, gc)
+            torch.cuda.synchronize()
+            for name, x in (("iters", it), ("c_out", co), ("w_tilde", wt), ("grad_w", gw), ("grad_c", gc)):
+                assert torch.equal(x, s[name]), (eps, rep, name)
+        seen.append(int(it.item()))
+    assert seen[1] == 1 and seen[0] > seen[2] > 1, seen
+
+
 def forward_after_a_failed_one():
     import ctypes
     hip = ctypes.CDLL([x for x in edkm._hip_runtimes()][0])
