@@ -389,8 +389,9 @@ edkm_status edkm_backward_batch_ex(int count, edkm_plan* const* plans, const uin
         return EDKM_OK;
     });
     if (st == EDKM_ERR_HIP) {
-        // a backward that did not run to its end may leave its table partials
-        // half-added: the next backward needs a new forward (which clears them)
+        // a backward that did not run to its end may leave values in the global
+        // keyed sums G (k_gather_grad, its last launch, clears them): the next
+        // backward needs a new forward, which clears them too
         for (int i = 0; i < count; ++i) impl(plans[i])->stage = COUNTED;
     }
     return st;

@@ -2662,8 +2662,17 @@ static uint32_t merge_chunks(const BatchArgs& b, int per = MERGE_ROWS) {
 }
 
 // A table phase over the launch's matrices: as few virtual blocks a block as let
-// all blocks run at a time (14 matrices at k = 8, forward and backward: 57 us
-// with one, 66 us with two).
+// all blocks run at a time, so that on an idle GPU no block waits for one that
+// has not started.  The calls of m matrices of 65,536 weights, 5 iterations, as
+// graph replays (forward + backward, us) with one | two | four a block:
+//   k = 8    m = 1: 32+49 | 42+70 | 53+85      m = 16: 42+77 | 43+78 | 50+92
+//            m = 17: 45+89 | 49+87 | 56+100    m = 28: 62+105 | 54+99 | 57+106
+//   k = 16   m = 12: 50+86 | 62+95 | 73+106    m = 16: 56+104 | 62+98 | 76+109
+//            m = 17: 68+113 | 75+149 | 89+130  m = 28: 82+145 | 86+154 | 91+134
+//   k = 2    m = 16: 41+67 | 37+64 | 39+69     m = 28: 49+90 | 42+76 | 42+78
+// One block's worth of waiting blocks would cost less than the second virtual
+// block at k = 16 from 17 to about 24 matrices (a backward of 113 to 129 us
+// against 130), and two would do better at k = 2 from 12 on: not taken.
 #define EDKM_TABLE(name, kern, bwd, ...)                                                         \
     do {                                                                                         \
         const dim3 tb_(T_THREADS);                                                               \
@@ -2801,7 +2810,11 @@ hipError_t launch_unique_inverse(BatchArgs& b, uint32_t grid_np, bool inverse, h
                                  const char** where, const PassEvents* ev) {
     (void)hipGetLastError();
     // 16 blocks share a matrix's output; fewer where that would have a large
-    // batch read its counts more often than the output takes to write
+    // batch read its counts more often than the output takes to write (replays of
+    // the call without inverse, 5.6M weights a matrix, us with 1 | 4 | 16 | 64
+    // blocks: 1 matrix 18.3 | 16.0 | 15.5 | 15.1, 7 matrices 18.0 | 16.8 | 17.5 |
+    // 17.5, 14 matrices 19.2 | 17.0 | 18.3 | 23.7, 28 matrices 19.7 | 16.5 | 20.5 |
+    // 39.9; with this rule 15.5, 15.8, 17.0 and 18.9)
     EDKM_LAUNCH("k_rank", k_rank, dim3(std::clamp(64 / b.count, 2, 16), b.count), dim3(1024), b);
     if (inverse) EDKM_NPASS(PASS_INVERSE, "k_inverse", k_inverse, dim3(grid_np), dim3(NP_THREADS), b);
     return hipSuccess;

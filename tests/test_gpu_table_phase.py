@@ -1,8 +1,8 @@
 """The table phases' launch shapes: batches at the edges of one block per
 virtual block, two virtual blocks per block and several launches give, bit for
-bit in the forward, what single calls give (which one launch of 64 blocks
-computes), and a forward repeated after one init_unique starts from clean
-exchange rows."""
+bit, what single calls give (which one launch of 64 blocks computes), and a
+forward or backward repeated after one init_unique, or after a failed forward,
+starts from clean exchange rows."""
 import os
 import subprocess
 import sys
@@ -43,9 +43,10 @@ def test_batches_equal_single_calls(bits, count):
         s = run(keys[i], c0[i], bits, inputs.TAU, iters, grad=g[i])
         torch.cuda.synchronize()
         assert torch.equal(co[i], s["c_out"]) and torch.equal(wt[i], s["w_tilde"]), i
-        # the backward's first sums are atomics: last bits differ
-        assert_close(gw[i].cpu().numpy(), s["grad_w"].cpu().numpy(), 1e-5, "grad_w %d" % i)
-        assert_close(gc[i].cpu().numpy(), s["grad_c"].cpu().numpy(), 1e-5, "grad_c %d" % i)
+        # bit for bit too: one workgroup takes all of a matrix in either call, and no
+        # gradient is beyond the keyed sum's fixed-point range (those that are go to
+        # G with float atomics, whose order is not fixed)
+        assert torch.equal(gw[i], s["grad_w"]) and torch.equal(gc[i], s["grad_c"]), i
 
 
 def test_forward_repeated_after_one_init():
