@@ -1125,13 +1125,14 @@ __global__ void __launch_bounds__(NP_THREADS) k_window(BatchArgs b) {
 // start.  The rows are exchanged inside the launch: each virtual block stores
 // its row with relaxed agent-scope stores and every block polls all rows until
 // none holds XW_EMPTY, so a word is its own arrival flag and no fence, counter
-// or cache write-back is involved.  A round of this takes 1.1 us for one
+// or cache write-back is involved.  The exchange alone takes 1.1 us for one
 // matrix and 1.8 us for seven (a probe), against 4-6 us for a dependent launch
-// with its drain, its dispatch and its argument and count loads.  Kernel times
+// with its drain, its dispatch and its argument and count loads; with the rows'
+// arithmetic a round takes 2.6-3.5 us at k = 8 (block timeline).  Kernel times
 // of the launches one phase took before -> of its one launch now: 4096x4096
 // at 3 bits, forward 23.1 -> 18.4 us, backward 24.2 -> 19.6 us; decoder layer
 // 28.2 -> 22.3 and 27.3 -> 25.1 us; an early stop among 30 iterations at 4
-// bits 123 -> 81 us.  What is left of a round is the stores reaching memory
+// bits 123 -> 81 us.  What is left of the exchange is the stores reaching memory
 // and the loads coming back.  (A grid barrier with release and acquire had
 // cost 10 us and more: it writes back and invalidates the XCDs' L2s.)
 //
@@ -1142,8 +1143,8 @@ __global__ void __launch_bounds__(NP_THREADS) k_window(BatchArgs b) {
 // of either origin, and decide the early stop from them), but its code is
 // inlined once for each of a block's virtual blocks and once more for the rows
 // of others: so nothing is left to the compiler's choice there.  Products are
-// added by a written fmaf, and contraction of others is off in these kernels
-// and in the functions that they share.
+// added by a written fmaf where they are fused, and contraction of others is off
+// in these kernels and in the functions that they share.
 //
 // Every row word is XW_EMPTY when a phase starts: the forward's rows are
 // emptied by k_init_zero and those it used again by k_gather_wt, the launch after
@@ -2148,8 +2149,8 @@ __global__ void __launch_bounds__(T_THREADS, (TABLE_BLOCKS<K, VB, true> / 256)) 
             if (t == T) {
                 gm = g_top;
             } else {
-                float x = (float)Cols<NC>::total(cols, jk) * inv_tau;
-                if (t + 1 == T) x = fmaf(e_top, inv_tau, x);
+                const float tot = (float)Cols<NC>::total(cols, jk);
+                float x = t + 1 == T ? fmaf(tot, inv_tau, e_top * inv_tau) : tot * inv_tau;
                 if (!(hS1 > 0.f)) x += gm;
                 gm = x;
             }
